@@ -83,7 +83,7 @@ struct Segment {
   int32_t c_begin;    // first constraint (planned order)
   int32_t c_count;    // constraints in the segment
   int32_t lit_base;   // offset of the segment's transposed literal block
-  int32_t k_fixed;    // > 0 when every constraint has this length
+  int32_t par_fixed;  // product kinds: the parameters (c_par) when every constraint has these, else 0
   int32_t cls_fixed;  // >= 0 when every constraint has this class
   int32_t m_max;      // DFT: largest number of complex nodes; PMF: widest window over the segment
 };
@@ -128,8 +128,9 @@ struct ProblemDev {
   const int32_t* litT;           // per segment: [KMAX][c_count] literal codes: variable in bits 0..30,
                                  // bit 31 set for a negated literal; a slot past the constraint's
                                  // end codes a pad row (variable >= n)
-  const int32_t* c_k;            // per constraint length (planned order)
   const int32_t* c_cls;          // per constraint class
+  const int32_t* c_par;          // per constraint of a product kind: two bf16 values, PROD1 b and c1,
+                                 // PROD2 c2 and c1 (high and low half)
   const float* c_w;              // per constraint weight
   const int32_t* row_ptr;        // planned-order CSR (extract / streaming engine)
   const int32_t* lit;            // planned-order literal codes

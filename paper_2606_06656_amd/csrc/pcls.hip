@@ -173,11 +173,11 @@ __device__ __forceinline__ cf grp_excl_c(cf v, int lig, int T) {
 template <int J>
 struct Fetched {
   int code[J];
-  int cls;
+  int cls;        // class; of a product kind its parameters (prod_params)
   float w;
 };
 
-template <int J, int KMAX>
+template <int KIND, int J, int KMAX>
 __device__ __forceinline__ void fetch_pair(const ProblemDev& P, const Segment& S, int c_local, int lig,
                                            Fetched<J>& f) {
   // A lane past the segment fetches its last pair (valid memory, no branch); the
@@ -191,7 +191,10 @@ __device__ __forceinline__ void fetch_pair(const ProblemDev& P, const Segment& S
 #pragma unroll
   for (int j = 0; j < J; ++j) f.code[j] = __builtin_amdgcn_raw_buffer_load_b32(rs, voff, j * S.c_count * 4, 0);
   const int c = S.c_begin + cl;
-  f.cls = S.cls_fixed >= 0 ? S.cls_fixed : P.c_cls[c];
+  if constexpr (KIND == KIND_PROD1 || KIND == KIND_PROD2)
+    f.cls = P.c_par[c];
+  else
+    f.cls = S.cls_fixed >= 0 ? S.cls_fixed : P.c_cls[c];
   f.w = P.unit_weights ? 1.f : P.c_w[c];
 }
 
@@ -240,20 +243,33 @@ struct ProdParams {
   float a, b, c1, c2;
 };
 
-__device__ __forceinline__ ProdParams prod_params(kptr<ClassRec> classes, int cls) {
-  return {classes[cls].a, classes[cls].b, classes[cls].c1, classes[cls].c2};
+// The parameters come with the constraint's codes, one chunk ahead, as two bf16
+// values in one word: PROD1 has b and c1 (a = 1 - |b|: the nodes are (1/2, 1/2),
+// (1/2, -1/2) and (0, 1)), PROD2 has c2 and c1 (both nodes fixed).  Reading them
+// from the class record instead made every chunk of a segment with several
+// classes wait for a load that depends on the fetched class, and with it, since
+// vector loads return in order, for the prefetch of the next chunk: a full
+// memory latency a chunk.
+template <int KIND>
+__device__ __forceinline__ ProdParams prod_params(int par) {
+  const float hi = __uint_as_float((unsigned)par & 0xffff0000u), lo = __uint_as_float((unsigned)par << 16);
+  if constexpr (KIND == KIND_PROD1)
+    return {1.f - fabsf(hi), hi, lo, 0.f};
+  else
+    return {0.5f, 0.5f, lo, hi};
 }
 
-// The same with the fixed-point scales folded in once per class: f = c fsc for
-// the objective, s1 = c1 b gsc and s2 = -c2/2 gsc for the gradient.  The scales
-// are powers of two, so every product equals the one formed by scaling last.
+// The same with the fixed-point scales folded in: f = c fsc for the objective,
+// s1 = c1 b gsc and s2 = -c2/2 gsc for the gradient.  The scales are powers of
+// two, so every product equals the one formed by scaling last.
 struct ProdConsts {
   float a, b, f1, f2, s1, s2;
 };
 
-__device__ __forceinline__ ProdConsts prod_consts(kptr<ClassRec> classes, int cls, float gsc, float fsc) {
-  const float a = classes[cls].a, b = classes[cls].b, c1 = classes[cls].c1, c2 = classes[cls].c2;
-  return {a, b, c1 * fsc, c2 * fsc, c1 * b * gsc, -0.5f * c2 * gsc};
+template <int KIND>
+__device__ __forceinline__ ProdConsts prod_consts(int par, float gsc, float fsc) {
+  const ProdParams p = prod_params<KIND>(par);
+  return {p.a, p.b, p.c1 * fsc, p.c2 * fsc, p.c1 * p.b * gsc, -0.5f * p.c2 * gsc};
 }
 
 // Slots past a constraint's end code a pad row whose factor is exactly 1 (the
@@ -943,10 +959,9 @@ __device__ __forceinline__ void run_segment_r2(const ProblemDev& P, const Segmen
   const int t2 = lane & ((1 << (logT - 1)) - 1);
   const int sub = lane >> (logT - 1);
   const int per_wave = kWave >> (logT - 1);
-  kptr<ClassRec> classes = kconst(P.classes);
-  const bool uni = S.cls_fixed >= 0;
+  const bool uni = S.par_fixed != 0;
   ProdConsts pc_uni{};
-  if (uni) pc_uni = prod_consts(classes, S.cls_fixed, gsc, fsc);
+  if (uni) pc_uni = prod_consts<KIND>(S.par_fixed, gsc, fsc);
   auto claim = [&]() {
     int b = 0;
     if (lane == 0) b = atomicAdd(ctr, U * per_wave);
@@ -954,7 +969,7 @@ __device__ __forceinline__ void run_segment_r2(const ProblemDev& P, const Segmen
   };
   auto fetch = [&](int b, FetchedU<J, U>& f) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) fetch_pair<J, KMAX>(P, S, b + u * per_wave + sub, 0, f.p[u]);
+    for (int u = 0; u < U; ++u) fetch_pair<KIND, J, KMAX>(P, S, b + u * per_wave + sub, 0, f.p[u]);
   };
   int base = claim();
   FetchedU<J, U> cur;
@@ -970,10 +985,8 @@ __device__ __forceinline__ void run_segment_r2(const ProblemDev& P, const Segmen
       if (u > 0 && b_u >= S.c_count) break;
       const Fetched<J>& fp = cur.p[u];
       const bool valid = b_u + sub < S.c_count;
-      const int c0 = __builtin_amdgcn_readfirstlane(fp.cls);
-      const bool chunk_uni = uni || !__any(valid && fp.cls != c0);
       if (valid) {
-        const ProdConsts pc = uni ? pc_uni : prod_consts(classes, chunk_uni ? c0 : fp.cls, gsc, fsc);
+        const ProdConsts pc = uni ? pc_uni : prod_consts<KIND>(fp.cls, gsc, fsc);
         prod_pair_r2<KIND == KIND_PROD2 ? 2 : 1, KMAX, UW>(fp, t2, logT, xs, gs, fca, fcb, pc);
       }
     }
@@ -1017,12 +1030,6 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
   const int lig = (lane >> logT) & (G - 1);
   const int sub = lane >> (logT + LG);
   const int per_wave = kWave >> (logT + LG);  // pairs one wave covers side by side
-  kptr<ClassRec> classes = kconst(P.classes);
-  const bool uni = S.cls_fixed >= 0;
-  ProdParams pp_uni{};
-  if constexpr (KIND == KIND_PROD1 || KIND == KIND_PROD2) {
-    if (uni) pp_uni = prod_params(classes, S.cls_fixed);
-  }
   // Software pipeline: the next chunk of U * per_wave constraints is claimed
   // and its literal codes are loaded before the current chunk is evaluated, so
   // the load latency overlaps the LDS and ALU work of the current chunk.
@@ -1033,7 +1040,7 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
   };
   auto fetch = [&](int b, FetchedU<J, U>& f) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) fetch_pair<J, KMAX>(P, S, b + u * per_wave + sub, lig, f.p[u]);
+    for (int u = 0; u < U; ++u) fetch_pair<KIND, J, KMAX>(P, S, b + u * per_wave + sub, lig, f.p[u]);
   };
   int base = claim();
   FetchedU<J, U> cur;
@@ -1052,10 +1059,6 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
       if (u > 0 && b_u >= S.c_count) break;  // wave-uniform: the rest of the chunk is past the segment
       const Fetched<J>& fp = cur.p[u];
       const bool valid = b_u + sub < S.c_count;
-      // constraints are sorted by class inside a segment, so most chunks hold
-      // one class: then its parameters are read once per wave with scalar loads
-      const int c0 = __builtin_amdgcn_readfirstlane(fp.cls);  // lane 0 holds a valid pair
-      const bool chunk_uni = uni || !__any(valid && fp.cls != c0);
       auto eval_pair = [&](auto& sink, const Fetched<J>& f) {
         if constexpr (KIND == KIND_DFT || (KIND == KIND_PMF && KMAX > 8)) {
           // lanes take turns by class (the first remaining lane's class each
@@ -1076,8 +1079,11 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
             }
           }
         } else if constexpr (KIND == KIND_PMF) {
+          // constraints are sorted by class inside a segment, so most chunks hold
+          // one class: then its record is read once per wave with scalar loads
+          const int c0 = __builtin_amdgcn_readfirstlane(f.cls);
+          const int cls = S.cls_fixed >= 0 || !__any(f.cls != c0) ? c0 : f.cls;
           // window width of the segment (uniform): 2, 3 or 4 counts
-          const int cls = chunk_uni ? c0 : f.cls;
           if (S.m_max <= 2) {
             pmf_pair<KMAX, 2>(P, cls, f, t, logT, xs, sink, fchunk, gsc, fsc);
           } else if (S.m_max == 3) {
@@ -1086,7 +1092,7 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
             pmf_pair<KMAX, 4>(P, cls, f, t, logT, xs, sink, fchunk, gsc, fsc);
           }
         } else {
-          const ProdParams pp = uni ? pp_uni : prod_params(classes, chunk_uni ? c0 : f.cls);
+          const ProdParams pp = prod_params<KIND>(f.cls);
           prod_pair<KIND == KIND_PROD2 ? 2 : 1, KMAX, G>(f, lig, t, logT, P.n, xs, sink, fchunk, gsc, fsc, pp);
         }
       };
@@ -1347,7 +1353,7 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
     kptr<Segment> segs = kconst(P.segments);
     for (int sg = 0; sg < n_seg; ++sg) {
       const Segment S{segs[sg].kind,    segs[sg].bucket, segs[sg].c_begin,   segs[sg].c_count,
-                      segs[sg].lit_base, segs[sg].k_fixed, segs[sg].cls_fixed, segs[sg].m_max};
+                      segs[sg].lit_base, segs[sg].par_fixed, segs[sg].cls_fixed, segs[sg].m_max};
       run_any_segment<MAXB>(P, S, xs, gs, facc, A.gsc, A.fsc, tid, logT, ctr + sg);
     }
     if constexpr (!kDefer) deposit(facc, set_of(0));
@@ -1471,7 +1477,7 @@ __global__ void __launch_bounds__(1024) stats_kernel(ProblemDev P, const float* 
   kptr<Segment> segs = kconst(P.segments);
   for (int sg = 0; sg < P.n_segments; ++sg) {
     const Segment S{segs[sg].kind,    segs[sg].bucket, segs[sg].c_begin,   segs[sg].c_count,
-                    segs[sg].lit_base, segs[sg].k_fixed, segs[sg].cls_fixed, segs[sg].m_max};
+                    segs[sg].lit_base, segs[sg].par_fixed, segs[sg].cls_fixed, segs[sg].m_max};
     run_any_segment<MAXB, unsigned int, true>(P, S, xs, nullptr, facc, 1.f, 0.f, (int)threadIdx.x, 0, ctr + sg, so);
   }
 }
@@ -1514,8 +1520,8 @@ __device__ __forceinline__ ProblemDev load_problem(kptr<BatchInst> bi) {
   P.nodes = bi->P.nodes;
   P.sp = bi->P.sp;
   P.litT = bi->P.litT;
-  P.c_k = bi->P.c_k;
   P.c_cls = bi->P.c_cls;
+  P.c_par = bi->P.c_par;
   P.c_w = bi->P.c_w;
   P.row_ptr = bi->P.row_ptr;
   P.lit = bi->P.lit;
@@ -2173,8 +2179,8 @@ int32_t pcls_upload(pcls_problem* p, void* d_ws, size_t bytes, void* stream) {
   D.nodes = (const NodeRec*)(b + p->off_nodes);
   D.sp = (const int8_t*)(b + p->off_sp);
   D.litT = (const int32_t*)(b + p->off_litT);
-  D.c_k = (const int32_t*)(b + p->off_ck);
   D.c_cls = (const int32_t*)(b + p->off_ccls);
+  D.c_par = (const int32_t*)(b + p->off_cpar);
   D.c_w = (const float*)(b + p->off_cw);
   D.row_ptr = (const int32_t*)(b + p->off_rowptr);
   D.lit = (const int32_t*)(b + p->off_lit);

@@ -320,6 +320,18 @@ static void dft_weights(const std::vector<int>& sp, ClassRec& C, std::vector<Nod
   }
 }
 
+// Parameters of a product class in one word: two bf16 values, all of them exact
+// (0, +-1/2, +-1, +-2).
+static int32_t product_params(const ClassRec& C) {
+  auto top = [](float v) {
+    uint32_t u;
+    std::memcpy(&u, &v, sizeof u);
+    return u & 0xffff0000u;
+  };
+  const float hi = C.kind == KIND_PROD1 ? C.b : C.c2;
+  return (int32_t)(top(hi) | (top(C.c1) >> 16));
+}
+
 static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* lit, const int8_t* type,
@@ -513,6 +525,7 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
   P->perm = order;
   P->c_k.resize(m);
   P->c_cls.resize(m);
+  P->c_par.assign((size_t)m, 0);
   P->c_w.resize(m);
   P->row_ptr.resize((size_t)m + 1);
   P->lit.resize((size_t)L);
@@ -542,14 +555,18 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
     S.kind = C0.kind;
     S.bucket = b;
     S.c_begin = j;
-    S.k_fixed = C0.k;
     S.cls_fixed = P->c_cls[j];
+    const bool product = C0.kind == KIND_PROD1 || C0.kind == KIND_PROD2;
+    S.par_fixed = product ? product_params(C0) : 0;
     S.m_max = 0;
     while (e < m) {
       const ClassRec& C = P->classes[P->c_cls[e]];
       if (C.kind != S.kind || bucket_of(C.k, P->bucket_table) != b) break;
-      if (C.k != S.k_fixed) S.k_fixed = 0;
       if (P->c_cls[e] != S.cls_fixed) S.cls_fixed = -1;
+      if (product) {
+        P->c_par[e] = product_params(C);
+        if (P->c_par[e] != S.par_fixed) S.par_fixed = 0;
+      }
       if (C.kind == KIND_DFT) S.m_max = std::max(S.m_max, C.n_nodes);
       if (C.kind == KIND_PMF) S.m_max = std::max(S.m_max, C.nyquist);
       ++e;
@@ -609,8 +626,8 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
   P->off_nodes = place(sizeof(NodeRec) * P->nodes.size());
   P->off_sp = place(P->sp.size());
   P->off_litT = place(sizeof(int32_t) * P->litT.size());
-  P->off_ck = place(sizeof(int32_t) * (size_t)m);
   P->off_ccls = place(sizeof(int32_t) * (size_t)m);
+  P->off_cpar = place(sizeof(int32_t) * (size_t)m);
   P->off_cw = place(sizeof(float) * (size_t)m);
   P->off_rowptr = place(sizeof(int32_t) * ((size_t)m + 1));
   P->off_lit = place(sizeof(int32_t) * (size_t)L);
@@ -626,8 +643,8 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
   put(P->off_nodes, P->nodes.data(), sizeof(NodeRec) * P->nodes.size());
   put(P->off_sp, P->sp.data(), P->sp.size());
   put(P->off_litT, P->litT.data(), sizeof(int32_t) * P->litT.size());
-  put(P->off_ck, P->c_k.data(), sizeof(int32_t) * (size_t)m);
   put(P->off_ccls, P->c_cls.data(), sizeof(int32_t) * (size_t)m);
+  put(P->off_cpar, P->c_par.data(), sizeof(int32_t) * (size_t)m);
   put(P->off_cw, P->c_w.data(), sizeof(float) * (size_t)m);
   put(P->off_rowptr, P->row_ptr.data(), sizeof(int32_t) * ((size_t)m + 1));
   put(P->off_lit, P->lit.data(), sizeof(int32_t) * (size_t)L);
