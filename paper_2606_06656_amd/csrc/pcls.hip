@@ -948,6 +948,39 @@ struct FetchedU {
   Fetched<J> p[U];
 };
 
+// The chunks of a segment that one wave claims, software-pipelined: while a chunk
+// is evaluated the next one's literal codes are loading, into the other of two
+// register sets (the loop is unrolled by two: copying one set to the other would
+// cost a move per code and wait for the loads at the end of every chunk).  With
+// AHEAD the claim runs one chunk further ahead still: its LDS atomic otherwise
+// waits, at the start of every chunk, behind the previous chunk's gradient
+// atomics.  Heavy chunks keep the later claim, which spreads them better.
+template <bool AHEAD, class F, class CLAIM, class FETCH, class EVAL>
+__device__ __forceinline__ void run_chunks(int count, CLAIM claim, FETCH fetch, EVAL eval) {
+  F f0, f1;
+  int base = __builtin_amdgcn_readfirstlane(claim());
+  if (base >= count) return;
+  int ahead = 0;
+  if constexpr (AHEAD) ahead = claim();
+  fetch(base, f0);
+  auto next = [&]() {
+    if constexpr (!AHEAD) return __builtin_amdgcn_readfirstlane(claim());
+    const int b = __builtin_amdgcn_readfirstlane(ahead);
+    ahead = claim();
+    return b;
+  };
+  for (;;) {
+    const int nbase = next();
+    fetch(nbase, f1);
+    eval(base, f0);
+    if (nbase >= count) break;
+    base = next();
+    fetch(base, f0);
+    eval(nbase, f1);
+    if (base >= count) break;
+  }
+}
+
 // The two-restarts-per-lane variant of run_segment for short product kinds.
 template <int KIND, int KMAX, bool UW, class AT>
 __device__ __forceinline__ void run_segment_r2(const ProblemDev& P, const Segment& S, const float* xs, AT* gs,
@@ -962,22 +995,16 @@ __device__ __forceinline__ void run_segment_r2(const ProblemDev& P, const Segmen
   const bool uni = S.par_fixed != 0;
   ProdConsts pc_uni{};
   if (uni) pc_uni = prod_consts<KIND>(S.par_fixed, gsc, fsc);
-  auto claim = [&]() {
+  auto claim = [&]() {  // lane 0 holds the claimed chunk
     int b = 0;
     if (lane == 0) b = atomicAdd(ctr, U * per_wave);
-    return __builtin_amdgcn_readfirstlane(b);
+    return b;
   };
   auto fetch = [&](int b, FetchedU<J, U>& f) {
 #pragma unroll
     for (int u = 0; u < U; ++u) fetch_pair<KIND, J, KMAX>(P, S, b + u * per_wave + sub, 0, f.p[u]);
   };
-  int base = claim();
-  FetchedU<J, U> cur;
-  fetch(base, cur);
-  while (base < S.c_count) {
-    const int nbase = claim();
-    FetchedU<J, U> nxt;
-    fetch(nbase, nxt);
+  auto eval = [&](int base, const FetchedU<J, U>& cur) {
     float fca = 0.f, fcb = 0.f;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -992,9 +1019,8 @@ __device__ __forceinline__ void run_segment_r2(const ProblemDev& P, const Segmen
     }
     facc.even += fixed_term(fca);
     facc.odd += fixed_term(fcb);
-    cur = nxt;
-    base = nbase;
-  }
+  };
+  run_chunks<true, FetchedU<J, U>>(S.c_count, claim, fetch, eval);
 }
 
 // Per-constraint gradient statistics (statistics kernel only): 64-bit
@@ -1030,25 +1056,16 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
   const int lig = (lane >> logT) & (G - 1);
   const int sub = lane >> (logT + LG);
   const int per_wave = kWave >> (logT + LG);  // pairs one wave covers side by side
-  // Software pipeline: the next chunk of U * per_wave constraints is claimed
-  // and its literal codes are loaded before the current chunk is evaluated, so
-  // the load latency overlaps the LDS and ALU work of the current chunk.
-  auto claim = [&]() {
+  auto claim = [&]() {  // lane 0 holds the claimed chunk
     int b = 0;
     if (lane == 0) b = atomicAdd(ctr, U * per_wave);
-    return __builtin_amdgcn_readfirstlane(b);
+    return b;
   };
   auto fetch = [&](int b, FetchedU<J, U>& f) {
 #pragma unroll
     for (int u = 0; u < U; ++u) fetch_pair<KIND, J, KMAX>(P, S, b + u * per_wave + sub, lig, f.p[u]);
   };
-  int base = claim();
-  FetchedU<J, U> cur;
-  fetch(base, cur);
-  while (base < S.c_count) {
-    const int nbase = claim();
-    FetchedU<J, U> nxt;
-    fetch(nbase, nxt);
+  auto eval = [&](int base, const FetchedU<J, U>& cur) {
     // A chunk (aligned, fixed pairs per lane, fixed order) sums its objective
     // terms in FP32 and adds one exact fixed-point term: the result does not
     // depend on which wave claimed the chunk.
@@ -1116,9 +1133,9 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
       }
     }
     facc.own += fixed_term(fchunk);
-    cur = nxt;
-    base = nbase;
-  }
+  };
+  constexpr bool kAhead = KIND == KIND_PROD1 || KIND == KIND_PROD2 || (KIND == KIND_PMF && KMAX <= 8);
+  run_chunks<kAhead, FetchedU<J, U>>(S.c_count, claim, fetch, eval);
 }
 
 #define PCLS_BUCKET_CASES(KIND, X) \
