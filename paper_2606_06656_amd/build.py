@@ -10,6 +10,8 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -18,7 +20,7 @@ SOURCES = ["pcls.hip", "plan.cpp", "mpnn.hip"]
 ARCH = os.environ.get("PCLS_OFFLOAD_ARCH", "gfx950")
 
 HIP_FLAGS = [
-    "-O3", "-std=c++17", "-fPIC", "-shared", f"--offload-arch={ARCH}",
+    "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # work claims are single-lane atomics on one LDS word: the pass that turns
     # uniform-address atomics into a wave reduction only adds instructions there
@@ -34,16 +36,31 @@ def hipcc() -> str:
     return "hipcc"
 
 
+def objects():
+    """(object name, source, extra flags) of every compilation: the variants of the
+    engine's kernels are compiled side by side."""
+    out = []
+    for maxb in ("kMaxbAll", "kMaxbMid", "kMaxbShort"):
+        for bits, acc in ((32, "unsigned int"), (64, "unsigned long long")):
+            flags = [f"-DPCLS_VARIANT_MAXB={maxb}", f"-DPCLS_VARIANT_ACC={acc}"]
+            out.append((f"pcls_{maxb}_{bits}.o", "pcls.hip", flags + (["-DPCLS_VARIANT_STATS"] if bits == 32 else [])))
+    return out + [(src.rsplit(".", 1)[0] + ".o", src, []) for src in SOURCES]
+
+
 def build(verbose: bool = False) -> str:
-    srcs = [os.path.join(CSRC, s) for s in SOURCES]
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        if res.returncode != 0:
+            sys.stderr.write(res.stdout + res.stderr)
+            raise RuntimeError("hipcc failed building libpcls.so")
+
     tmp = LIB + ".tmp"
-    cmd = [hipcc(), *HIP_FLAGS, "-o", tmp, *srcs]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        sys.stderr.write(res.stdout + res.stderr)
-        raise RuntimeError("hipcc failed building libpcls.so")
+    with tempfile.TemporaryDirectory() as work, ThreadPoolExecutor(min(8, os.cpu_count() or 1)) as pool:
+        jobs = [(os.path.join(work, o), os.path.join(CSRC, src), flags) for o, src, flags in objects()]
+        list(pool.map(lambda j: run([hipcc(), *HIP_FLAGS, *j[2], "-c", j[1], "-o", j[0]]), jobs))
+        run([hipcc(), f"--offload-arch={ARCH}", "-fPIC", "-shared", "-o", tmp, *(j[0] for j in jobs)])
     os.replace(tmp, LIB)
     return LIB
 

@@ -22,7 +22,11 @@ namespace pcls {
 const char* last_error();
 }
 
-namespace {
+// This file is compiled several times: with PCLS_VARIANT_MAXB and
+// PCLS_VARIANT_ACC defined it holds one variant of the engine's kernels (they
+// take minutes to compile one after another), without them everything else.
+namespace pcls {
+namespace engine {
 
 constexpr int kWave = 64;
 
@@ -1499,13 +1503,6 @@ __global__ void __launch_bounds__(1024) stats_kernel(ProblemDev P, const float* 
   }
 }
 
-// acc (planned order, scale 2^s) -> out[caller's constraint index]
-__global__ void stats_finish_kernel(const unsigned long long* __restrict__ acc, const int32_t* __restrict__ perm,
-                                    int m, double inv, float* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < m) out[perm[i]] = (float)((double)(long long)acc[i] * inv);
-}
-
 // ------------------------------------------------------------ batched engine
 // Many problems (instances) and their restart tiles in one persistent launch.
 // Work items (instance, first restart, tile size) are claimed from a counter in
@@ -1586,6 +1583,46 @@ __global__ void __launch_bounds__(1024) batch_kernel(const BatchInst* __restrict
     resident_tile<MAXB, AT>(P, A, lds_raw);
     __syncthreads();
   }
+}
+
+#ifdef PCLS_VARIANT_MAXB
+
+template __global__ void tile_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC>(ProblemDev, TileArgs);
+template __global__ void batch_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC>(const BatchInst*, const BatchItem*, int,
+                                                                           unsigned int*, float, int, int);
+#ifdef PCLS_VARIANT_STATS
+template __global__ void stats_kernel<PCLS_VARIANT_MAXB>(ProblemDev, const float*, int, StatsOut);
+#endif
+
+}  // namespace engine
+}  // namespace pcls
+
+#else
+
+#define PCLS_EXTERN_VARIANT(MAXB)                                                                                  \
+  extern template __global__ void tile_kernel<MAXB, unsigned int>(ProblemDev, TileArgs);                           \
+  extern template __global__ void tile_kernel<MAXB, unsigned long long>(ProblemDev, TileArgs);                     \
+  extern template __global__ void batch_kernel<MAXB, unsigned int>(const BatchInst*, const BatchItem*, int,        \
+                                                                   unsigned int*, float, int, int);                \
+  extern template __global__ void batch_kernel<MAXB, unsigned long long>(const BatchInst*, const BatchItem*, int,  \
+                                                                         unsigned int*, float, int, int);          \
+  extern template __global__ void stats_kernel<MAXB>(ProblemDev, const float*, int, StatsOut);
+PCLS_EXTERN_VARIANT(kMaxbShort)
+PCLS_EXTERN_VARIANT(kMaxbMid)
+PCLS_EXTERN_VARIANT(kMaxbAll)
+
+}  // namespace engine
+}  // namespace pcls
+
+using namespace pcls::engine;
+
+namespace {
+
+// acc (planned order, scale 2^s) -> out[caller's constraint index]
+__global__ void stats_finish_kernel(const unsigned long long* __restrict__ acc, const int32_t* __restrict__ perm,
+                                    int m, double inv, float* __restrict__ out) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < m) out[perm[i]] = (float)((double)(long long)acc[i] * inv);
 }
 
 __global__ void fill_u32_kernel(unsigned int* p, unsigned int v, int count) {
@@ -2558,3 +2595,5 @@ int32_t pcls_destroy(pcls_problem* p) {
 const char* pcls_last_error(void) { return pcls::last_error(); }
 
 }  // extern "C"
+
+#endif  // PCLS_VARIANT_MAXB
