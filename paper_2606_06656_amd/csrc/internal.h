@@ -16,13 +16,14 @@ namespace pcls {
 //           FE = c0 + c1 * prod_i (a + b y_i)
 //   PROD2 - two real nodes (sp constant on 1..k-1):
 //           FE = c0 + c1 * prod_i (1+y_i)/2 + c2 * prod_i (1-y_i)/2
-//   DFT   - the K = k+1 complex roots of unity: FE = sum_m chat_m prod_i(alpha_m + beta_m y_i)
+//   DFT   - any spectrum: the count distribution of each lane's literals, combined across
+//           a lane group at the K = KMAX+1 complex roots of unity of the length bucket
 //   PMF   - sp constant outside a window of w counts at one end (thresholds,
 //           at-most-one, exactly-kappa near an end), w <= 4 for k <= 8 (one lane
 //           per pair) and w <= KMAX/2 of the length bucket for 8 < k <= 48 (lane
 //           groups): with C the number of true literals (or of false ones),
 //           FE = c0 + sum_{c < w} d_c Pr[C = c], from a truncated Poisson-binomial
-//           recursion and its adjoint (no products of complex factors)
+//           recursion and its adjoint (no complex nodes)
 //   CONST - sp constant: FE = c0, no literal work
 enum Kind : int32_t { KIND_PROD1 = 0, KIND_PROD2 = 1, KIND_DFT = 2, KIND_PMF = 3, KIND_CONST = 4 };
 constexpr int kNumKinds = 5;
@@ -51,17 +52,22 @@ constexpr int kMaxSegments = 4 * kNumBuckets;  // (kind, bucket) pairs of the no
 constexpr int kPadRows = 64;
 
 // Lanes per (constraint, restart) pair: one lane holds up to 16 literals of a
-// product kind or 8 of the DFT and PMF kinds (register budget at 4 waves per SIMD);
-// longer constraints spread over G lanes (a power of two) of at most 8 literals
-// each (6 for the buckets 12, 24, ..., 192).
-constexpr int lane_groups(int kmax) {
+// DFT or short product constraint or 8 of the PMF kind (register budget at 4 waves
+// per SIMD); longer constraints spread over G lanes (a power of two) of at most
+// 8 literals each (6 for the buckets 12, 24, ..., 192), the DFT kind of at most 16
+// (12).
+constexpr int lane_groups(int kmax, int per_lane = 8) {
   int g = 1;
-  while (kmax > 8 * g) g *= 2;
+  while (kmax > per_lane * g) g *= 2;
   return g;
 }
 constexpr int group_size(int kind, int kmax) {
-  return (kmax <= 8 || (kind != KIND_DFT && kind != KIND_PMF && kmax <= 16)) ? 1 : lane_groups(kmax);
+  if (kind == KIND_DFT) return lane_groups(kmax, 16);
+  return (kmax <= 8 || (kind != KIND_PMF && kmax <= 16)) ? 1 : lane_groups(kmax);
 }
+// What a constraint limits the tile width by (64 / width lanes are left for its
+// group): the lanes of at most 8 literals, also where a kind uses fewer.
+constexpr int tile_group(int kind, int kmax) { return kind == KIND_DFT ? lane_groups(kmax) : group_size(kind, kmax); }
 
 // Bucket tables: which of the compiled lengths a plan uses.  Table 0 uses all of
 // them; table 1 only the exact ones up to 8 and the powers of two above (fewer
@@ -85,33 +91,35 @@ struct Segment {
   int32_t lit_base;   // offset of the segment's transposed literal block
   int32_t par_fixed;  // product kinds: the parameters (c_par) when every constraint has these, else 0
   int32_t cls_fixed;  // >= 0 when every constraint has this class
-  int32_t m_max;      // DFT: largest number of complex nodes; PMF: widest window over the segment
+  int32_t m_max;      // PMF: widest window over the segment
+  int32_t z_off;      // DFT over a lane group: the bucket's node powers (entry of the node table)
 };
 
 // Per constraint class (type, k, param).
 struct ClassRec {
   int32_t kind;
   int32_t k;
-  int32_t n_nodes;   // DFT: complex nodes m = 1..n_nodes
-  int32_t node_off;  // DFT: offset into the node table (entries)
-  int32_t nyquist;   // DFT: 1 when K = k + 1 is even (real node at omega = -1); PMF: window w
+  int32_t n_nodes;   // DFT, PMF: entries of the node table
+  int32_t node_off;  // DFT, PMF: offset into the node table (entries)
+  int32_t window;    // PMF: window w
   int32_t sp_off;    // offset of sp[0..k] (int8) in the spectrum table
   float a, b;        // PROD1 node factor a + b y
-  float c1, c2;      // PROD1 / PROD2 product weights; DFT: c1 = chat_{K/2} (Nyquist weight)
+  float c1, c2;      // PROD1 / PROD2 product weights
   float c0;          // constant term (folded into the per-problem constant on device)
   float pad;
 };
 
-// DFT node m of a class: factor alpha + beta y, weight 2*chat_m for the value
-// and 2*chat_m*beta_m for the gradient (the 2 covers the conjugate node K - m).
-// A PMF class of k <= 8 literals has one record: {d_0, d_1, d_2, d_3, h, 0, 0, 0},
-// where the counted event of literal i has probability 1/2 - h y_i (h = 1/2:
-// true, -1/2: false); a longer one has five records read as 40 floats:
-// d_0..d_31 (zero past its window), h, a threshold flag (d constant on the
-// window), then padding.
+// Entry of the node table: eight floats, read by kind.
+//   DFT over a lane group of J literals a lane, K = KMAX + 1: a class has the
+//     KMAX/2 weights W_m = 2 chat_m (re, im; the 2 covers the conjugate node K - m),
+//     and the bucket the powers z_m^1..z_m^J of every node (J real, J imaginary parts).
+//   DFT on one lane: a class has sp_t - sp_k for t = 0..KMAX (0 past k).
+//   PMF of k <= 8 literals: one entry {d_0, d_1, d_2, d_3, h, 0, 0, 0}, where the
+//     counted event of literal i has probability 1/2 - h y_i (h = 1/2: true, -1/2:
+//     false); a longer one has five: d_0..d_31 (zero past its window), h, a
+//     threshold flag (d constant on the window), then padding.
 struct NodeRec {
-  float ar, ai, br, bi;
-  float wr, wi, gr, gi;
+  float f[8];
 };
 
 // Device view of a planned problem (passed by value to kernels).
@@ -130,7 +138,8 @@ struct ProblemDev {
                                  // end codes a pad row (variable >= n)
   const int32_t* c_cls;          // per constraint class
   const int32_t* c_par;          // per constraint of a product kind: two bf16 values, PROD1 b and c1,
-                                 // PROD2 c2 and c1 (high and low half)
+                                 // PROD2 c2 and c1 (high and low half); of a DFT one: its class's
+                                 // node table entry
   const float* c_w;              // per constraint weight
   const int32_t* row_ptr;        // planned-order CSR (extract / streaming engine)
   const int32_t* lit;            // planned-order literal codes

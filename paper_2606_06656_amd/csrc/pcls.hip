@@ -177,7 +177,7 @@ __device__ __forceinline__ cf grp_excl_c(cf v, int lig, int T) {
 template <int J>
 struct Fetched {
   int code[J];
-  int cls;        // class; of a product kind its parameters (prod_params)
+  int cls;        // class; of a product kind its parameters (prod_params), of a DFT one its node table entry
   float w;
 };
 
@@ -195,7 +195,7 @@ __device__ __forceinline__ void fetch_pair(const ProblemDev& P, const Segment& S
 #pragma unroll
   for (int j = 0; j < J; ++j) f.code[j] = __builtin_amdgcn_raw_buffer_load_b32(rs, voff, j * S.c_count * 4, 0);
   const int c = S.c_begin + cl;
-  if constexpr (KIND == KIND_PROD1 || KIND == KIND_PROD2)
+  if constexpr (KIND != KIND_PMF)
     f.cls = P.c_par[c];
   else
     f.cls = S.cls_fixed >= 0 ? S.cls_fixed : P.c_cls[c];
@@ -335,86 +335,6 @@ __device__ __forceinline__ void prod_pair(const Fetched<KMAX / G>& fp, int lig, 
   }
 }
 
-// Generic kind: FE - chat_0 = sum_{m=1}^{M} Re(2 chat_m Q_m) [+ chat_{K/2} prod y];
-// dFE/dy_i = sum_m Re(2 chat_m beta_m prod_{j != i}(alpha_m + beta_m y_j)) [+ chat_{K/2} prod_{j != i} y_j].
-// cls is the pair's class; when the caller passes a wave-uniform value the class
-// record and the node table are read with scalar loads.
-template <int KMAX, int G, class SK>
-__device__ __forceinline__ void dft_pair(const ProblemDev& P, int m_max, int cls, const Fetched<KMAX / G>& fp,
-                                         int lig, int t, int logT, const float* xs, SK& sink, float& fchunk,
-                                         float gsc, float fsc) {
-  constexpr int J = KMAX / G;
-  constexpr bool kExact = KMAX <= 8;  // buckets up to 8 hold a single length
-  const int T = 1 << logT;
-  kptr<ClassRec> classes = kconst(P.classes);
-  const int nyquist = classes[cls].nyquist;
-  const float cn = classes[cls].c1;
-  const int node_off = classes[cls].node_off;
-  const int nn = classes[cls].n_nodes;
-
-  unsigned el[J];
-  float y[J], g[J];
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const int code = fp.code[j];
-    el[j] = lit_off(code, logT, t);  // pad slots read y = 1: factor alpha + beta = 1 exactly
-    y[j] = flip(x_at(xs, el[j]), lit_sign(code));
-    g[j] = 0.f;
-  }
-  float fe = 0.f;
-  if (nyquist) {  // real node omega^(K/2) = -1: factor y, padded slots hold y = 1
-    float pre[J];
-    float run = 1.f;
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-      pre[j] = run;
-      run *= y[j];
-    }
-    const float ex = grp_excl<G>(run, lig, T);
-    fe = cn * (run * ex);
-    const float sc = cn * ex;
-    float suf = 1.f;
-#pragma unroll
-    for (int j = J - 1; j >= 0; --j) {
-      g[j] = sc * pre[j] * suf;
-      suf *= y[j];
-    }
-  }
-  kptr<NodeRec> nd = kconst(P.nodes) + node_off;
-  for (int mm = 0; mm < m_max; ++mm) {
-    if (mm < nn) {
-      const NodeRec N{nd[mm].ar, nd[mm].ai, nd[mm].br, nd[mm].bi, nd[mm].wr, nd[mm].wi, nd[mm].gr, nd[mm].gi};
-      cf pre[J];
-      cf run{1.f, 0.f};
-#pragma unroll
-      for (int j = 0; j < J; ++j) {
-        pre[j] = run;
-        const cf f{fmaf(N.br, y[j], N.ar), fmaf(N.bi, y[j], N.ai)};
-        run = cmul(run, f);
-      }
-      const cf ex = grp_excl_c<G>(run, lig, T);  // the other lanes' node products
-      const cf tot = cmul(run, ex);
-      fe = fmaf(N.wr, tot.r, fmaf(-N.wi, tot.i, fe));
-      // The gradient of literal j is Re(gw * prefix_j * suffix_j), gw the node's
-      // gradient weight: carrying S_j = gw * (other lanes) * (lane suffix)_j down
-      // the literals leaves one real part of a product per literal.
-      cf S = cmul(cf{N.gr, N.gi}, ex);
-#pragma unroll
-      for (int j = J - 1; j >= 0; --j) {
-        g[j] = fmaf(pre[j].r, S.r, fmaf(-pre[j].i, S.i, g[j]));  // Re(pre_j * S_j)
-        const cf f{fmaf(N.br, y[j], N.ar), fmaf(N.bi, y[j], N.ai)};
-        S = cmul(S, f);
-      }
-    }
-  }
-  if (lig == 0) fchunk = fmaf(fp.w * fsc, fe, fchunk);
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const float gv = (fp.w * gsc) * g[j];
-    sink.add(el[j], flip(gv, lit_sign(fp.code[j])), fp.code[j]);
-  }
-}
-
 // Waves claim chunks of a segment's constraints from an LDS counter (one chunk
 // = the constraints one wave covers: 64 / (G T)), so heavy and light items
 // spread over the waves as they finish; segments are ordered heaviest first.
@@ -434,11 +354,11 @@ __device__ __forceinline__ void pmf_pair(const ProblemDev& P, int cls, const Fet
   static_assert(W >= 1 && W <= kPmfWindow, "window");
   kptr<ClassRec> classes = kconst(P.classes);
   kptr<NodeRec> nd = kconst(P.nodes) + classes[cls].node_off;
-  const float dall[kPmfWindow] = {nd[0].ar, nd[0].ai, nd[0].br, nd[0].bi};
+  const float dall[kPmfWindow] = {nd[0].f[0], nd[0].f[1], nd[0].f[2], nd[0].f[3]};
   float d[W];
 #pragma unroll
   for (int c = 0; c < W; ++c) d[c] = dall[c];
-  const float h = nd[0].wr;
+  const float h = nd[0].f[4];
 
   unsigned el[J];
   float pi[J], pre[J][W];
@@ -695,6 +615,134 @@ __device__ __forceinline__ void conv_trunc(const float (&u)[NU], const float (&v
   }
 }
 
+// Generic kind: any spectrum.  With pi_i = (1 - y_i)/2 the probability that
+// literal i is true and T the number of true ones, FE = sum_t sp_t Pr[T = t].
+// A lane turns its J literals into their count distribution q (counts 0..J: two
+// halves by the recursion, then one convolution), and FE is linear in q:
+// FE - c0 = sum_j q(j) D(j), D the adjoint that carries everything the other
+// lanes hold.  One lane (k <= 16): D = sp - sp_k itself.  A group: the
+// characteristic function of T at z_m = exp(2 pi i m / K), K = KMAX + 1, is the
+// product over the lanes of Q(z_m) = sum_j q(j) z_m^j, so with ex_m the other
+// lanes' product and W_m twice the spectrum's inverse transform,
+// D(j) = sum_{m=1}^{KMAX/2} Re(W_m ex_m z_m^j).  The gradient of a literal is the
+// adjoint of its half's recursion started from D convolved with the other half.
+// Bound by VALU issue.  A node costs 2J operations for Q, 2J + 1 for D, about 12
+// a level for the exchange: 5 a literal at J = 16, where carrying the node's
+// complex prefix and suffix products through the literals took about 19; the
+// recursions add about 38 a literal once.  J = 16 and not 8: fewer lanes
+// exchange less, and the live q, D and codes still fit 128 VGPRs.  The nodes are
+// those of the bucket, not of the class, so lanes of different classes run
+// together and only load their own W_m (one node ahead).  Measured: 4 x 5 x 64
+// constraints of 64 to 256 literals at 256 restarts 590 -> 388 us an evaluation;
+// the 77 constraints above 48 literals of the long-support instance (20000
+// variables, 4096 restarts) 0.32 -> 0.16 ms of a step.
+template <int N, class SK>
+__device__ __forceinline__ void dft_scatter(const float* gp, const int* code, float wg, int logT, int t, SK& sink) {
+  const float coef = -0.5f * wg;  // dFE/dy_j = -1/2 dFE/dpi_j
+#pragma unroll
+  for (int j = N - 1; j >= 0; --j) sink.add(lit_off(code[j], logT, t), flip(coef * gp[j], lit_sign(code[j])), code[j]);
+}
+// The literals of one half from the adjoint lam of its count distribution.
+template <int H, class SK>
+__device__ __forceinline__ void dft_half(const float* pi, float (&lam)[H + 1], const int* code, float wg, int logT,
+                                         int t, SK& sink) {
+  float p[H], pre[H][H + 1], q[H + 1], gp[H];
+#pragma unroll
+  for (int j = 0; j < H; ++j) {
+    p[j] = pi[j];
+    // opaque: the recursion is run again here; its distributions of the first
+    // run would otherwise be kept across the node loop, in scratch memory
+    asm volatile("" : "+v"(p[j]));
+  }
+  count_forward<H, H + 1>(p, pre, q);
+  count_adjoint<H, H + 1>(p, pre, lam, gp);
+  dft_scatter<H>(gp, code, wg, logT, t, sink);
+}
+template <int KMAX, int G, class SK>
+__device__ __forceinline__ void dft_pair(const ProblemDev& P, int z_off, const Fetched<KMAX / G>& fp, int lig, int t,
+                                         int logT, const float* xs, SK& sink, float& fchunk, float gsc, float fsc) {
+  constexpr int J = KMAX / G;
+  const int T = 1 << logT;
+  const unsigned node_off = (unsigned)fp.cls;
+  float pi[J];
+#pragma unroll
+  for (int j = 0; j < J; ++j)  // a pad slot reads y = 1: pi = 0, it adds nothing to the count
+    pi[j] = fmaf(-0.5f, flip(x_at(xs, lit_off(fp.code[j], logT, t)), lit_sign(fp.code[j])), 0.5f);
+  float fe = 0.f;
+  if constexpr (J <= 8) {
+    static_assert(G == 1, "one lane up to 8 literals");
+    const float* sp = reinterpret_cast<const float*>(P.nodes + node_off);
+    float pre[J][J + 1], q[J + 1], lam[J + 1];
+    count_forward<J, J + 1>(pi, pre, q);
+#pragma unroll
+    for (int c = 0; c <= J; ++c) {
+      lam[c] = sp[c];
+      fe = fmaf(q[c], lam[c], fe);
+    }
+    float gp[J];
+    count_adjoint<J, J + 1>(pi, pre, lam, gp);
+    dft_scatter<J>(gp, fp.code, fp.w * gsc, logT, t, sink);
+  } else {
+    constexpr int H = J / 2;
+    static_assert(J % 4 == 0 && J <= 16, "halves");
+    float qa[H + 1], qb[H + 1], D[J + 1];
+    count_only<H, H + 1>(pi, qa);
+    count_only<H, H + 1>(pi + H, qb);
+    if constexpr (G == 1) {
+      const float* sp = reinterpret_cast<const float*>(P.nodes + node_off);
+#pragma unroll
+      for (int c = 0; c <= J; ++c) D[c] = sp[c];
+    } else {
+      float q[J + 1];
+      conv_trunc(qa, qb, q);
+#pragma unroll
+      for (int c = 0; c <= J; ++c) D[c] = 0.f;
+      kptr<float> z = reinterpret_cast<kptr<float>>(kconst(P.nodes) + z_off);
+      // this lane's W_m: wave-uniform base (scalar registers) plus a 32-bit lane offset
+      const char* wb = reinterpret_cast<const char*>(P.nodes);
+      const unsigned woff = node_off * (unsigned)sizeof(NodeRec);
+      float2 w = *reinterpret_cast<const float2*>(wb + woff);
+      for (int m = 0; m < KMAX / 2; ++m) {
+        const float2 w_next = *reinterpret_cast<const float2*>(wb + (m + 1 < KMAX / 2 ? 8 * (m + 1) : 0) + woff);
+        cf Q{q[0], 0.f};
+#pragma unroll
+        for (int j = 1; j <= J; ++j) {
+          Q.r = fmaf(q[j], z[j - 1], Q.r);
+          Q.i = fmaf(q[j], z[J + j - 1], Q.i);
+        }
+        const cf S = cmul(cf{w.x, w.y}, grp_excl_c<G>(Q, lig, T));
+        D[0] += S.r;
+#pragma unroll
+        for (int j = 1; j <= J; ++j) D[j] = fmaf(S.r, z[j - 1], fmaf(-S.i, z[J + j - 1], D[j]));
+        w = w_next;
+        z += 2 * J;
+      }
+    }
+    // per half: DA(a) = sum_b qb(b) D(a+b), DB(b) = sum_a qa(a) D(a+b)
+    __builtin_amdgcn_sched_barrier(0);
+    float DA[H + 1], DB[H + 1];
+#pragma unroll
+    for (int a = 0; a <= H; ++a) {
+      float sa = 0.f, sb = 0.f;
+#pragma unroll
+      for (int b = 0; b <= H; ++b) {
+        sa = fmaf(qb[b], D[a + b], sa);
+        sb = fmaf(qa[b], D[a + b], sb);
+      }
+      DA[a] = sa;
+      DB[a] = sb;
+      fe = fmaf(qa[a], sa, fe);
+    }
+    // one half after the other (the barriers keep the scheduler from running
+    // both at once, whose intermediate distributions do not fit the registers)
+    __builtin_amdgcn_sched_barrier(0);
+    dft_half<H>(pi, DA, fp.code, fp.w * gsc, logT, t, sink);
+    __builtin_amdgcn_sched_barrier(0);
+    dft_half<H>(pi + H, DB, fp.code + H, fp.w * gsc, logT, t, sink);
+  }
+  if (lig == 0) fchunk = fmaf(fp.w * fsc, fe, fchunk);
+}
+
 // The lane at xor distance 4 T in the lane's group of eight.  With T = 1 the
 // group is an 8-lane half-row: the lower quad reads 4 lanes up, the upper quad 4
 // lanes down (two DPP row shifts and a select); otherwise a wave shuffle.  The
@@ -740,7 +788,7 @@ __device__ __forceinline__ void pmfg8_pair(const ProblemDev& P, int cls, const F
   const int T = 1 << logT;
   kptr<ClassRec> classes = kconst(P.classes);
   kptr<float> dt = reinterpret_cast<kptr<float>>(kconst(P.nodes) + classes[cls].node_off);
-  const int w = classes[cls].nyquist;
+  const int w = classes[cls].window;
   const float h = dt[32];
   const bool thr = dt[33] != 0.f;
 
@@ -955,20 +1003,28 @@ struct FetchedU {
 // The chunks of a segment that one wave claims, software-pipelined: while a chunk
 // is evaluated the next one's literal codes are loading, into the other of two
 // register sets (the loop is unrolled by two: copying one set to the other would
-// cost a move per code and wait for the loads at the end of every chunk).  With
-// AHEAD the claim runs one chunk further ahead still: its LDS atomic otherwise
+// cost a move per code and wait for the loads at the end of every chunk).  The
+// claim runs one chunk further ahead still: its LDS atomic otherwise
 // waits, at the start of every chunk, behind the previous chunk's gradient
-// atomics.  Heavy chunks keep the later claim, which spreads them better.
-template <bool AHEAD, class F, class CLAIM, class FETCH, class EVAL>
+// atomics.  A heavy chunk (tens of microseconds) is fetched when its turn comes:
+// the latency does not show, and the registers of a second set do.
+template <bool HEAVY, class F, class CLAIM, class FETCH, class EVAL>
 __device__ __forceinline__ void run_chunks(int count, CLAIM claim, FETCH fetch, EVAL eval) {
-  F f0, f1;
   int base = __builtin_amdgcn_readfirstlane(claim());
+  if constexpr (HEAVY) {
+    while (base < count) {
+      F f;
+      fetch(base, f);
+      eval(base, f);
+      base = __builtin_amdgcn_readfirstlane(claim());
+    }
+    return;
+  }
   if (base >= count) return;
-  int ahead = 0;
-  if constexpr (AHEAD) ahead = claim();
+  F f0, f1;
+  int ahead = claim();
   fetch(base, f0);
   auto next = [&]() {
-    if constexpr (!AHEAD) return __builtin_amdgcn_readfirstlane(claim());
     const int b = __builtin_amdgcn_readfirstlane(ahead);
     ahead = claim();
     return b;
@@ -1024,7 +1080,7 @@ __device__ __forceinline__ void run_segment_r2(const ProblemDev& P, const Segmen
     facc.even += fixed_term(fca);
     facc.odd += fixed_term(fcb);
   };
-  run_chunks<true, FetchedU<J, U>>(S.c_count, claim, fetch, eval);
+  run_chunks<false, FetchedU<J, U>>(S.c_count, claim, fetch, eval);
 }
 
 // Per-constraint gradient statistics (statistics kernel only): 64-bit
@@ -1081,17 +1137,16 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
       const Fetched<J>& fp = cur.p[u];
       const bool valid = b_u + sub < S.c_count;
       auto eval_pair = [&](auto& sink, const Fetched<J>& f) {
-        if constexpr (KIND == KIND_DFT || (KIND == KIND_PMF && KMAX > 8)) {
+        if constexpr (KIND == KIND_DFT) {
+          dft_pair<KMAX, G>(P, S.z_off, f, lig, t, logT, xs, sink, fchunk, gsc, fsc);
+        } else if constexpr (KIND == KIND_PMF && KMAX > 8) {
           // lanes take turns by class (the first remaining lane's class each
-          // round; one round for a class-uniform chunk), so the class record,
-          // node table and window coefficients are always read with scalar loads
+          // round; one round for a class-uniform chunk), so the class record and
+          // the window coefficients are always read with scalar loads
           for (;;) {
             const int cc = __builtin_amdgcn_readfirstlane(f.cls);
             if (f.cls == cc) {
-              if constexpr (KIND == KIND_DFT) {
-                kptr<ClassRec> cr = kconst(P.classes);
-                dft_pair<KMAX, G>(P, cr[cc].n_nodes, cc, f, lig, t, logT, xs, sink, fchunk, gsc, fsc);
-              } else if constexpr (G == 8) {
+              if constexpr (G == 8) {
                 pmfg8_pair<KMAX>(P, cc, f, lig, t, logT, xs, sink, fchunk, gsc, fsc);
               } else {
                 pmfg_pair<KMAX, G>(P, cc, f, lig, t, logT, xs, sink, fchunk, gsc, fsc);
@@ -1138,8 +1193,8 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
     }
     facc.own += fixed_term(fchunk);
   };
-  constexpr bool kAhead = KIND == KIND_PROD1 || KIND == KIND_PROD2 || (KIND == KIND_PMF && KMAX <= 8);
-  run_chunks<kAhead, FetchedU<J, U>>(S.c_count, claim, fetch, eval);
+  constexpr bool kHeavy = KIND == KIND_DFT || (KIND == KIND_PMF && KMAX > 8);
+  run_chunks<kHeavy, FetchedU<J, U>>(S.c_count, claim, fetch, eval);
 }
 
 #define PCLS_BUCKET_CASES(KIND, X) \
@@ -1374,7 +1429,7 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
     kptr<Segment> segs = kconst(P.segments);
     for (int sg = 0; sg < n_seg; ++sg) {
       const Segment S{segs[sg].kind,    segs[sg].bucket, segs[sg].c_begin,   segs[sg].c_count,
-                      segs[sg].lit_base, segs[sg].par_fixed, segs[sg].cls_fixed, segs[sg].m_max};
+                      segs[sg].lit_base, segs[sg].par_fixed, segs[sg].cls_fixed, segs[sg].m_max, segs[sg].z_off};
       run_any_segment<MAXB>(P, S, xs, gs, facc, A.gsc, A.fsc, tid, logT, ctr + sg);
     }
     if constexpr (!kDefer) deposit(facc, set_of(0));
@@ -1498,7 +1553,7 @@ __global__ void __launch_bounds__(1024) stats_kernel(ProblemDev P, const float* 
   kptr<Segment> segs = kconst(P.segments);
   for (int sg = 0; sg < P.n_segments; ++sg) {
     const Segment S{segs[sg].kind,    segs[sg].bucket, segs[sg].c_begin,   segs[sg].c_count,
-                    segs[sg].lit_base, segs[sg].par_fixed, segs[sg].cls_fixed, segs[sg].m_max};
+                    segs[sg].lit_base, segs[sg].par_fixed, segs[sg].cls_fixed, segs[sg].m_max, segs[sg].z_off};
     run_any_segment<MAXB, unsigned int, true>(P, S, xs, nullptr, facc, 1.f, 0.f, (int)threadIdx.x, 0, ctr + sg, so);
   }
 }

@@ -260,64 +260,69 @@ static bool pmf_counts_false_of(const std::vector<NodeRec>& nodes, const ClassRe
   return rec[32] < 0.f;
 }
 
-// Inverse-DFT weights over the K = k + 1 roots of unity.  With
-// Q_m = prod_i (alpha_m + beta_m y_i), alpha_m = (1 + w^m)/2, beta_m = (1 - w^m)/2,
-// w = exp(2 pi i / K), Q_m is the characteristic function of T at 2 pi m / K,
-// so Pr[T = t] = (1/K) sum_m Q_m w^-tm and FE = sum_m chat_m Q_m with
-// chat_m = (1/K) sum_t sp_t w^-tm.  The angles use exact integer reduction
-// (t m mod K) and FP64 arithmetic; results are rounded once to float32.
-static void dft_weights(const std::vector<int>& sp, ClassRec& C, std::vector<NodeRec>& nodes) {
-  const int k = (int)sp.size() - 1;
-  const int K = k + 1;
-  const double two_pi = 6.283185307179586476925286766559;
-  auto chat = [&](int m, double& re, double& im) {
-    re = im = 0.0;
-    for (int t = 0; t <= k; ++t) {
-      long r = ((long)t * m) % K;
-      double ang = two_pi * (double)r / (double)K;
-      re += sp[t] * std::cos(ang);
-      im -= sp[t] * std::sin(ang);
+// DFT kind.  One lane (bucket up to 16): sp_t - sp_k.  A lane group: the
+// inverse-DFT weights over the K = kmax + 1 roots of unity of the bucket.  With
+// Q_m the characteristic function of the number of true literals T <= k at
+// 2 pi m / K, Pr[T = t] = (1/K) sum_m Q_m w^-tm and FE = sum_m chat_m Q_m with
+// chat_m = (1/K) sum_t sp_t w^-tm; the spectrum past k, which no count reaches, is
+// continued by sp_k (the weights' magnitudes stay those of the shape up to k).
+// The angles use exact integer reduction (t m mod K) and FP64 arithmetic; results
+// are rounded once to float32.
+struct Roots {  // cos and sin of 2 pi r / K
+  std::vector<double> c, s;
+  explicit Roots(int K) : c((size_t)K), s((size_t)K) {
+    const double two_pi = 6.283185307179586476925286766559;
+    for (int r = 0; r < K; ++r) {
+      c[(size_t)r] = std::cos(two_pi * (double)r / (double)K);
+      s[(size_t)r] = std::sin(two_pi * (double)r / (double)K);
     }
-    re /= K;
-    im /= K;
-  };
-  double c0r, c0i;
-  chat(0, c0r, c0i);
-  C.c0 = (float)c0r;
-  C.nyquist = (K % 2 == 0) ? 1 : 0;
-  C.n_nodes = (K - 1) / 2;  // complex nodes 1..(K-1)/2; K even adds the real node K/2
+  }
+};
+
+static void put_floats(const std::vector<float>& f, std::vector<NodeRec>& nodes) {
+  const size_t at = nodes.size();
+  nodes.resize(at + (f.size() + 7) / 8, NodeRec{});
+  std::memcpy(nodes[at].f, f.data(), f.size() * sizeof(float));
+}
+
+static void dft_class(const std::vector<int>& sp, int kmax, const Roots& w, ClassRec& C, std::vector<NodeRec>& nodes) {
+  const int k = (int)sp.size() - 1;
+  std::vector<float> rec;
+  if (group_size(KIND_DFT, kmax) == 1) {
+    C.c0 = (float)sp[(size_t)k];
+    for (int t = 0; t <= kmax; ++t) rec.push_back(t < k ? (float)(sp[(size_t)t] - sp[(size_t)k]) : 0.f);
+  } else {
+    const int K = kmax + 1;
+    auto at = [&](int t) { return sp[(size_t)std::min(t, k)]; };
+    double c0 = 0.0;
+    for (int t = 0; t < K; ++t) c0 += at(t);
+    C.c0 = (float)(c0 / K);
+    for (int m = 1; m <= kmax / 2; ++m) {
+      double re = 0.0, im = 0.0;
+      for (int t = 0, r = 0; t < K; ++t, r = (r + m) % K) {
+        re += at(t) * w.c[(size_t)r];
+        im -= at(t) * w.s[(size_t)r];
+      }
+      rec.push_back((float)(2.0 * re / K));
+      rec.push_back((float)(2.0 * im / K));
+    }
+  }
   C.node_off = (int32_t)nodes.size();
-  for (int m = 1; m <= C.n_nodes; ++m) {
-    double wr, wi;
-    chat(m, wr, wi);
-    double ang = two_pi * (double)m / (double)K;
-    double er = std::cos(ang), ei = std::sin(ang);
-    // alpha + beta = 1 exactly in float32 (the larger real part is rounded, the
-    // other is 1 minus it, exact by Sterbenz), so a pad slot (y = 1) has the
-    // factor 1 + 0i exactly
-    float far = (float)(0.5 * (1.0 + er)), fbr = (float)(0.5 * (1.0 - er));
-    if (far >= 0.5f)
-      fbr = 1.0f - far;
-    else
-      far = 1.0f - fbr;
-    const float fai = (float)(0.5 * ei);
-    const double ar = far, br = fbr, ai = fai, bi = -(double)fai;
-    NodeRec nd;
-    nd.ar = far;
-    nd.ai = fai;
-    nd.br = fbr;
-    nd.bi = -fai;
-    nd.wr = (float)(2.0 * wr);
-    nd.wi = (float)(2.0 * wi);
-    nd.gr = (float)(2.0 * (wr * br - wi * bi));
-    nd.gi = (float)(2.0 * (wr * bi + wi * br));
-    nodes.push_back(nd);
+  put_floats(rec, nodes);
+  C.n_nodes = (int32_t)nodes.size() - C.node_off;
+}
+
+// The powers z_m^1..z_m^J of the nodes of a bucket (J literals a lane).
+static int32_t dft_powers(int kmax, const Roots& w, std::vector<NodeRec>& nodes) {
+  const int J = kmax / group_size(KIND_DFT, kmax), K = kmax + 1;
+  std::vector<float> rec;
+  for (int m = 1; m <= kmax / 2; ++m) {
+    for (int j = 1; j <= J; ++j) rec.push_back((float)w.c[(size_t)(j * m % K)]);
+    for (int j = 1; j <= J; ++j) rec.push_back((float)w.s[(size_t)(j * m % K)]);
   }
-  if (C.nyquist) {
-    double s = 0.0;
-    for (int t = 0; t <= k; ++t) s += (t & 1) ? -sp[t] : sp[t];
-    C.c1 = (float)(s / K);
-  }
+  const int32_t at = (int32_t)nodes.size();
+  put_floats(rec, nodes);
+  return at;
 }
 
 // Parameters of a product class in one word: two bf16 values, all of them exact
@@ -395,6 +400,11 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
   // ---- classes
   std::map<ClassKey, int> class_of;
   std::vector<int> cls_orig((size_t)m);
+  std::map<int, Roots> roots_of;  // by bucket length
+  auto roots = [&](int kmax) -> const Roots& {
+    auto it = roots_of.find(kmax);
+    return it != roots_of.end() ? it->second : roots_of.emplace(kmax, kmax + 1).first->second;
+  };
   double f_const = 0.0;
   for (int c = 0; c < m; ++c) {
     int ty = type[c];
@@ -408,16 +418,16 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
       ClassRec C{};
       C.k = k;
       classify(sp, force_generic, P->bucket_table, C);
-      if (C.kind == KIND_DFT) dft_weights(sp, C, P->nodes);
+      if (C.kind == KIND_DFT) {
+        const int kmax = kBucketKmax[bucket_of(k, P->bucket_table)];
+        dft_class(sp, kmax, roots(kmax), C, P->nodes);
+      }
       if (C.kind == KIND_PMF && k <= kPmfMaxK) {
         NodeRec N{};
         float d[kPmfWindow], h;
-        C.nyquist = pmf_window(sp, d, &h, kPmfWindow);  // PMF: the window w (counts kept)
-        N.ar = d[0];
-        N.ai = d[1];
-        N.br = d[2];
-        N.bi = d[3];
-        N.wr = h;
+        C.window = pmf_window(sp, d, &h, kPmfWindow);  // counts kept
+        for (int c = 0; c < kPmfWindow; ++c) N.f[c] = d[c];
+        N.f[4] = h;
         C.c0 = (float)(h > 0.f ? sp[k] : sp[0]);
         C.node_off = (int32_t)P->nodes.size();
         C.n_nodes = 1;
@@ -427,7 +437,7 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
         float rec[40] = {};
         float h;
         const int w = pmf_window(sp, rec, &h, 32);
-        C.nyquist = w;
+        C.window = w;
         rec[32] = h;
         bool thr = true;  // d constant on the window
         for (int c = 1; c < w; ++c)
@@ -567,8 +577,8 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
         P->c_par[e] = product_params(C);
         if (P->c_par[e] != S.par_fixed) S.par_fixed = 0;
       }
-      if (C.kind == KIND_DFT) S.m_max = std::max(S.m_max, C.n_nodes);
-      if (C.kind == KIND_PMF) S.m_max = std::max(S.m_max, C.nyquist);
+      if (C.kind == KIND_DFT) P->c_par[e] = C.node_off;
+      if (C.kind == KIND_PMF) S.m_max = std::max(S.m_max, C.window);
       ++e;
     }
     S.c_count = e - j;
@@ -594,7 +604,8 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
     }
     const int G = group_size(S.kind, kmax);
     if (kmax > 8 && kmax <= 64) balance_long_slots(P->litT.data() + S.lit_base, S.c_count, kmax, G);
-    P->max_group = std::max(P->max_group, G);
+    if (S.kind == KIND_DFT && G > 1) S.z_off = dft_powers(kmax, roots(kmax), P->nodes);
+    P->max_group = std::max(P->max_group, tile_group(S.kind, kmax));
     P->max_bucket = std::max(P->max_bucket, b);
     P->segments.push_back(S);
     j = e;
@@ -606,7 +617,7 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
   std::stable_sort(P->segments.begin(), P->segments.end(), [](const Segment& a, const Segment& b) {
     auto cost = [](const Segment& s) {
       const int k = kBucketKmax[s.bucket];
-      return s.kind == KIND_DFT ? 4 * k * (s.m_max + 1)
+      return s.kind == KIND_DFT ? (group_size(KIND_DFT, k) == 1 ? 6 * k : k * (k / 2 + 8))
              : s.kind == KIND_PMF ? (k <= kPmfMaxK ? 6 * k : k * (k / 2 + 2))
              : (s.kind == KIND_PROD2 ? 2 * k : k);
     };
