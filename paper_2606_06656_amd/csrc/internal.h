@@ -106,7 +106,11 @@ struct ClassRec {
   float a, b;        // PROD1 node factor a + b y
   float c1, c2;      // PROD1 / PROD2 product weights
   float c0;          // constant term (folded into the per-problem constant on device)
-  float pad;
+  // Which counts t of true literals violate the constraint (extraction): every
+  // type's spectrum alternates or changes sign at most twice, so
+  // [violated] = v0 ^ (vpar & t & 1) ^ [t >= t1] ^ [t >= t2], packed as t1 in bits
+  // 0..8, t2 in bits 9..17 (511 where there is none), v0 in bit 18, vpar in bit 19.
+  uint32_t violated;
 };
 
 // Entry of the node table: eight floats, read by kind.
@@ -143,6 +147,8 @@ struct ProblemDev {
   const float* c_w;              // per constraint weight
   const int32_t* row_ptr;        // planned-order CSR (extract / streaming engine)
   const int32_t* lit;            // planned-order literal codes
+  const uint32_t* c_viol;        // per constraint: ClassRec::violated
+  int32_t const_unsat;           // violated constraints among those of constant spectrum
   int32_t unit_weights;          // all weights 1.0
   int32_t max_k;
   const int32_t* occ;            // per variable: occurrences in non-constant constraints

@@ -337,6 +337,18 @@ static int32_t product_params(const ClassRec& C) {
   return (int32_t)(top(hi) | (top(C.c1) >> 16));
 }
 
+// Violated counts of a spectrum, packed (ClassRec::violated).
+static uint32_t violated_counts(const std::vector<int>& sp) {
+  const int k = (int)sp.size() - 1;
+  std::vector<uint32_t> turn;
+  for (int t = 1; t <= k; ++t)
+    if (sp[(size_t)t] != sp[(size_t)t - 1]) turn.push_back((uint32_t)t);
+  const uint32_t v0 = sp[0] > 0 ? 1u << 18 : 0u;
+  if (turn.size() > 2) return v0 | 1u << 19 | 511u << 9 | 511u;  // alternating: parity
+  turn.resize(2, 511u);
+  return v0 | turn[1] << 9 | turn[0];
+}
+
 static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* lit, const int8_t* type,
@@ -418,6 +430,7 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
       ClassRec C{};
       C.k = k;
       classify(sp, force_generic, P->bucket_table, C);
+      C.violated = violated_counts(sp);
       if (C.kind == KIND_DFT) {
         const int kmax = kBucketKmax[bucket_of(k, P->bucket_table)];
         dft_class(sp, kmax, roots(kmax), C, P->nodes);
@@ -536,6 +549,7 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
   P->c_k.resize(m);
   P->c_cls.resize(m);
   P->c_par.assign((size_t)m, 0);
+  P->c_viol.resize((size_t)m);
   P->c_w.resize(m);
   P->row_ptr.resize((size_t)m + 1);
   P->lit.resize((size_t)L);
@@ -545,6 +559,8 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
     int k = row_ptr[c + 1] - row_ptr[c];
     P->c_k[j] = k;
     P->c_cls[j] = cls_orig[c];
+    P->c_viol[j] = P->classes[(size_t)cls_orig[c]].violated;
+    if (P->classes[(size_t)cls_orig[c]].kind == KIND_CONST) P->const_unsat += (P->c_viol[j] >> 18) & 1u;
     P->c_w[j] = weight ? weight[c] : 1.0f;
     P->row_ptr[j + 1] = P->row_ptr[j] + k;
     for (int i = 0; i < k; ++i) {
@@ -639,6 +655,7 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
   P->off_litT = place(sizeof(int32_t) * P->litT.size());
   P->off_ccls = place(sizeof(int32_t) * (size_t)m);
   P->off_cpar = place(sizeof(int32_t) * (size_t)m);
+  P->off_cviol = place(sizeof(uint32_t) * (size_t)m);
   P->off_cw = place(sizeof(float) * (size_t)m);
   P->off_rowptr = place(sizeof(int32_t) * ((size_t)m + 1));
   P->off_lit = place(sizeof(int32_t) * (size_t)L);
@@ -656,6 +673,7 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
   put(P->off_litT, P->litT.data(), sizeof(int32_t) * P->litT.size());
   put(P->off_ccls, P->c_cls.data(), sizeof(int32_t) * (size_t)m);
   put(P->off_cpar, P->c_par.data(), sizeof(int32_t) * (size_t)m);
+  put(P->off_cviol, P->c_viol.data(), sizeof(uint32_t) * (size_t)m);
   put(P->off_cw, P->c_w.data(), sizeof(float) * (size_t)m);
   put(P->off_rowptr, P->row_ptr.data(), sizeof(int32_t) * ((size_t)m + 1));
   put(P->off_lit, P->lit.data(), sizeof(int32_t) * (size_t)L);

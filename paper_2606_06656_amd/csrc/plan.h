@@ -20,6 +20,8 @@ struct pcls_problem {
   std::vector<int8_t> sp;
   std::vector<int32_t> litT;
   std::vector<int32_t> c_k, c_cls, c_par;
+  std::vector<uint32_t> c_viol;
+  int32_t const_unsat = 0;
   std::vector<float> c_w;
   std::vector<int32_t> row_ptr, lit;   // planned order
   std::vector<int32_t> perm;           // planned index -> original constraint index
@@ -40,7 +42,7 @@ struct pcls_problem {
 
   // device image
   std::vector<uint8_t> image;
-  size_t off_segments = 0, off_classes = 0, off_nodes = 0, off_sp = 0, off_litT = 0, off_cpar = 0,
+  size_t off_segments = 0, off_classes = 0, off_nodes = 0, off_sp = 0, off_litT = 0, off_cpar = 0, off_cviol = 0,
          off_ccls = 0, off_cw = 0, off_rowptr = 0, off_lit = 0, off_occ = 0, off_perm = 0;
   void* d_ws = nullptr;
   size_t ws_bytes = 0;
