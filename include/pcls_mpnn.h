@@ -94,6 +94,37 @@ int32_t pcls_mpnn_adam(float* p, const float* g, float* m, float* v, int32_t cou
 /* y = bf16(x), nearest even. */
 int32_t pcls_mpnn_to_bf16(const float* x, uint16_t* y, int32_t count, void* hip_stream);
 
+/* The network's whole forward and backward pass.
+ *
+ * Graph: CSR in both directions (as pcls_mpnn_gather), features row-major with
+ * 32 columns.  cw / vw are the forward weights of the entries, cw_t / vw_t the
+ * transposed ones (backward pass only).
+ * Parameters (params float32, params_bf16 the rounded copy): flat, in the order
+ * Ev [64][32], ev [64], Ec [64][32], ec [64], per round W1 [64][64], bc [64],
+ * Wpn [128][64], W2 [64][64], bv [64], Upn [128][64], then wo [64], bo [1].
+ * acts: pcls_mpnn_forward_floats floats, written by the forward pass and read by
+ * the backward pass of the same graph; scratch: pcls_mpnn_backward_floats floats.
+ * params, params_bf16, acts, scratch and the features 16-byte aligned.  xhat and
+ * dxhat: n_vars floats.  grad: every parameter's gradient, flat, written (not
+ * accumulated).  Work is asynchronous on the stream; the graph struct is read
+ * during the call only. */
+typedef struct pcls_mpnn_graph {
+  int32_t n_vars, n_cons;
+  const float *feat_v, *feat_c;
+  const int32_t *cptr, *cidx;
+  const float *cw, *cw_t;
+  const int32_t *vptr, *vidx;
+  const float *vw, *vw_t;
+} pcls_mpnn_graph;
+
+size_t pcls_mpnn_forward_floats(int32_t n_vars, int32_t n_cons);
+size_t pcls_mpnn_backward_floats(int32_t n_vars, int32_t n_cons);
+int32_t pcls_mpnn_forward(const pcls_mpnn_graph* graph, const float* params, const uint16_t* params_bf16, float* acts,
+                          float* xhat, void* hip_stream);
+int32_t pcls_mpnn_backward(const pcls_mpnn_graph* graph, const float* params, const uint16_t* params_bf16,
+                           const float* acts, const float* xhat, const float* dxhat, float* grad, float* scratch,
+                           size_t scratch_floats, void* hip_stream);
+
 const char* pcls_mpnn_last_error(void);
 
 #ifdef __cplusplus

@@ -16,7 +16,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpcls.so")
-SOURCES = ["pcls.hip", "plan.cpp", "mpnn.hip"]
+SOURCES = ["pcls.hip", "plan.cpp", "mpnn.hip", "mpnn_net.hip"]
 ARCH = os.environ.get("PCLS_OFFLOAD_ARCH", "gfx950")
 
 HIP_FLAGS = [

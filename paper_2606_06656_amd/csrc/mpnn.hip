@@ -15,7 +15,7 @@
 
 #include "../../include/pcls_mpnn.h"
 
-namespace {
+namespace pcls_mpnn {
 
 thread_local std::string g_err;
 
@@ -30,6 +30,13 @@ int32_t hip_check(hipError_t e, const char* what) {
   g_err = std::string(what) + ": " + hipGetErrorString(e);
   return 5;
 }
+
+}  // namespace pcls_mpnn
+
+namespace {
+
+using pcls_mpnn::fail;
+using pcls_mpnn::hip_check;
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
@@ -329,7 +336,7 @@ __global__ void to_bf16_kernel(const float* __restrict__ x, uint16_t* __restrict
 // ======================================================================= C ABI
 extern "C" {
 
-const char* pcls_mpnn_last_error(void) { return g_err.c_str(); }
+const char* pcls_mpnn_last_error(void) { return pcls_mpnn::g_err.c_str(); }
 
 int32_t pcls_mpnn_gemm(const float* A, int32_t lda, int32_t N, int32_t K, const uint16_t* W, int32_t M,
                        int32_t trans_w, const float* bias, float* Y, int32_t ldy, int32_t beta, float* Y_relu,

@@ -37,6 +37,11 @@ N_TYPES = 7
 _bound = False
 
 
+class CGraph(ctypes.Structure):  # pcls_mpnn_graph
+    _fields_ = [("n_vars", ctypes.c_int32), ("n_cons", ctypes.c_int32)] + [
+        (f, ctypes.c_void_p) for f in ("feat_v", "feat_c", "cptr", "cidx", "cw", "cw_t", "vptr", "vidx", "vw", "vw_t")]
+
+
 def _lib():
     global _bound
     L = pcls.load_library()
@@ -74,6 +79,14 @@ def _lib():
         L.pcls_mpnn_adam.argtypes = [vp, vp, vp, vp, i32, f32, f32, f32, f32, i32, f32, vp, vp]
         L.pcls_mpnn_to_bf16.restype = i32
         L.pcls_mpnn_to_bf16.argtypes = [vp, vp, i32, vp]
+        for f in (L.pcls_mpnn_forward_floats, L.pcls_mpnn_backward_floats):
+            f.restype = sz
+            f.argtypes = [i32, i32]
+        gp = ctypes.POINTER(CGraph)
+        L.pcls_mpnn_forward.restype = i32
+        L.pcls_mpnn_forward.argtypes = [gp, vp, vp, vp, vp, vp]
+        L.pcls_mpnn_backward.restype = i32
+        L.pcls_mpnn_backward.argtypes = [gp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
         L.pcls_mpnn_last_error.restype = ctypes.c_char_p
         _bound = True
     return L
@@ -83,7 +96,8 @@ MPNN_EXPORTS = ["pcls_mpnn_gemm", "pcls_mpnn_gemm_tn_scratch", "pcls_mpnn_gemm_t
                 "pcls_mpnn_relu_grad", "pcls_mpnn_colsum_scratch", "pcls_mpnn_colsum", "pcls_mpnn_head_forward",
                 "pcls_mpnn_head_backward", "pcls_mpnn_head_grad_scratch", "pcls_mpnn_head_grad",
                 "pcls_mpnn_propose", "pcls_mpnn_mse_scratch", "pcls_mpnn_mse", "pcls_mpnn_adam",
-                "pcls_mpnn_to_bf16", "pcls_mpnn_last_error"]
+                "pcls_mpnn_to_bf16", "pcls_mpnn_forward_floats", "pcls_mpnn_backward_floats", "pcls_mpnn_forward",
+                "pcls_mpnn_backward", "pcls_mpnn_last_error"]
 
 
 def _ck(status):
@@ -230,6 +244,11 @@ class GraphBatch:
         self.vw_t = t(1.0 / klen[con_of[order]], torch.float32)
         self.device = device
 
+    def c_graph(self):
+        p = lambda t: t.data_ptr()  # noqa: E731
+        return CGraph(self.Nv, self.Nc, p(self.Fv), p(self.Fc), p(self.cptr), p(self.cidx), p(self.cw), p(self.cw_t),
+                      p(self.vptr), p(self.vidx), p(self.vw), p(self.vw_t))
+
     def slice_vars(self, x, k):
         return x[int(self.var_off[k]):int(self.var_off[k + 1])]
 
@@ -323,75 +342,21 @@ class MPNN:
 
     def forward(self, G: GraphBatch, keep=False):
         import torch
-        P, Nv, Nc, dev = self.P, G.Nv, G.Nc, G.device
-        e = lambda *s: torch.empty(*s, dtype=torch.float32, device=dev)  # noqa: E731
-        Zv0, Hv, Zc0, Hc = e(Nv, HID), e(Nv, HID), e(Nc, HID), e(Nc, HID)
-        gemm(G.Fv, FEAT, Nv, FEAT, P.wb("Ev"), HID, 0, P.w("ev"), Zv0, HID, 0, Hv)
-        gemm(G.Fc, FEAT, Nc, FEAT, P.wb("Ec"), HID, 0, P.w("ec"), Zc0, HID, 0, Hc)
-        caches = []
-        for l in range(LAYERS):
-            Pm, Zc, Hc2, Qm, Zv, Hv2 = e(Nv, 2 * HID), e(Nc, HID), e(Nc, HID), e(Nc, 2 * HID), e(Nv, HID), e(Nv, HID)
-            gemm(Hv, HID, Nv, HID, P.wb(f"Wpn_{l}"), 2 * HID, 0, None, Pm, 2 * HID)
-            gemm(Hc, HID, Nc, HID, P.wb(f"W1_{l}"), HID, 0, P.w(f"bc_{l}"), Zc, HID)
-            gather(G.cptr, G.cidx, G.cw, Nc, Pm, 2 * HID, Zc, HID, Hc2, 0)
-            gemm(Hc2, HID, Nc, HID, P.wb(f"Upn_{l}"), 2 * HID, 0, None, Qm, 2 * HID)
-            gemm(Hv, HID, Nv, HID, P.wb(f"W2_{l}"), HID, 0, P.w(f"bv_{l}"), Zv, HID)
-            gather(G.vptr, G.vidx, G.vw, Nv, Qm, 2 * HID, Zv, HID, Hv2, 0)
-            if keep:
-                caches.append((Hv, Hc, Zc, Hc2, Zv))
-            Hv, Hc = Hv2, Hc2
-        xhat = e(Nv)
-        head_forward(Hv, Nv, P.w("wo"), P.w("bo"), xhat)
+        L, P = _lib(), self.P
+        acts = torch.empty(L.pcls_mpnn_forward_floats(G.Nv, G.Nc) + 4, dtype=torch.float32, device=G.device)
+        xhat = torch.empty(G.Nv, dtype=torch.float32, device=G.device)
+        _ck(L.pcls_mpnn_forward(ctypes.byref(G.c_graph()), _p(P.master), _p(P.bf16), _p(acts), _p(xhat), _s()))
         if keep:
-            self._cache = (Zv0, Zc0, caches, Hv, xhat, G)
+            self._cache = (acts, xhat, G)
         return xhat
 
     def backward(self, dxhat):
         """Gradients of every parameter (written, not accumulated) from dL/dxhat."""
-        import torch
-        P, sc = self.P, self.scratch
-        Zv0, Zc0, caches, HvL, xhat, G = self._cache
-        Nv, Nc, dev = G.Nv, G.Nc, G.device
-        e = lambda *s: torch.empty(*s, dtype=torch.float32, device=dev)  # noqa: E731
-        dHv, dlogit = e(Nv, HID), e(Nv)
-        head_backward(xhat, dxhat, Nv, P.w("wo"), dHv, dlogit)
-        o_wo = P.offsets["wo"][0]
-        head_grad(HvL, dlogit, Nv, P.grad[o_wo:o_wo + HID + 1], sc)  # wo and bo are adjacent
-        dHc = None
-        for l in reversed(range(LAYERS)):
-            Hv, Hc, Zc, Hc2, Zv = caches[l]
-            dZv = e(Nv, HID)
-            relu_grad(dHv, Zv, dZv)
-            colsum(dZv, HID, Nv, P.g(f"bv_{l}"), sc)
-            gemm_tn(dZv, HID, Hv, HID, Nv, HID, HID, P.g(f"W2_{l}"), sc)
-            dHv_in = e(Nv, HID)
-            gemm(dZv, HID, Nv, HID, P.wb(f"W2_{l}"), HID, 1, None, dHv_in, HID)
-            dQ = e(Nc, 2 * HID)
-            gather(G.cptr, G.cidx, G.cw_t, Nc, dZv, HID, dQ, 2 * HID, None, 1)
-            gemm_tn(dQ, 2 * HID, Hc2, HID, Nc, 2 * HID, HID, P.g(f"Upn_{l}"), sc)
-            if dHc is None:
-                dHc = e(Nc, HID)
-                gemm(dQ, 2 * HID, Nc, 2 * HID, P.wb(f"Upn_{l}"), HID, 1, None, dHc, HID, 0)
-            else:
-                gemm(dQ, 2 * HID, Nc, 2 * HID, P.wb(f"Upn_{l}"), HID, 1, None, dHc, HID, 1)
-            dZc = e(Nc, HID)
-            relu_grad(dHc, Zc, dZc)
-            colsum(dZc, HID, Nc, P.g(f"bc_{l}"), sc)
-            gemm_tn(dZc, HID, Hc, HID, Nc, HID, HID, P.g(f"W1_{l}"), sc)
-            dHc_in = e(Nc, HID)
-            gemm(dZc, HID, Nc, HID, P.wb(f"W1_{l}"), HID, 1, None, dHc_in, HID)
-            dP = e(Nv, 2 * HID)
-            gather(G.vptr, G.vidx, G.vw_t, Nv, dZc, HID, dP, 2 * HID, None, 1)
-            gemm_tn(dP, 2 * HID, Hv, HID, Nv, 2 * HID, HID, P.g(f"Wpn_{l}"), sc)
-            gemm(dP, 2 * HID, Nv, 2 * HID, P.wb(f"Wpn_{l}"), HID, 1, None, dHv_in, HID, 1)
-            dHv, dHc = dHv_in, dHc_in
-        dZv0, dZc0 = e(Nv, HID), e(Nc, HID)
-        relu_grad(dHv, Zv0, dZv0)
-        relu_grad(dHc, Zc0, dZc0)
-        colsum(dZv0, HID, Nv, P.g("ev"), sc)
-        colsum(dZc0, HID, Nc, P.g("ec"), sc)
-        gemm_tn(dZv0, HID, G.Fv, FEAT, Nv, HID, FEAT, P.g("Ev"), sc)
-        gemm_tn(dZc0, HID, G.Fc, FEAT, Nc, HID, FEAT, P.g("Ec"), sc)
+        L, P = _lib(), self.P
+        acts, xhat, G = self._cache
+        buf, nb = self.scratch.get(4 * L.pcls_mpnn_backward_floats(G.Nv, G.Nc))
+        _ck(L.pcls_mpnn_backward(ctypes.byref(G.c_graph()), _p(P.master), _p(P.bf16), _p(acts), _p(xhat), _p(dxhat),
+                                 _p(P.grad), _p(buf), nb // 4, _s()))
 
     def mse_loss_grad(self, xhat, y):
         """dL/dxhat for L = mean (xhat - y)^2; returns (dxhat, loss tensor)."""
