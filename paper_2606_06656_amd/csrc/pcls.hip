@@ -86,10 +86,20 @@ struct FixedAcc<unsigned long long> {
 template <>
 struct FixedAcc<unsigned int> {
   // round to nearest (ties up) in one instruction: v_cvt_rpi computes floor(v + 1/2)
-  static __device__ __forceinline__ void add(unsigned int* p, float v) {
+  static __device__ __forceinline__ int round(float v) {
     int r;
     asm("v_cvt_rpi_i32_f32 %0, %1" : "=v"(r) : "v"(v));
-    atomicAdd(p, (unsigned int)r);
+    return r;
+  }
+  static __device__ __forceinline__ void add(unsigned int* p, float v) { atomicAdd(p, (unsigned int)round(v)); }
+  // Pairs: in the short-constraint variants with T >= 2 the words of restarts 2t
+  // and 2t + 1 of a variable are one 64-bit integer, low + 2^32 high, so one LDS
+  // atomic adds both restarts' terms (two 32-bit ones took 16 LDS cycles a wave,
+  // one 64-bit one 12).  A negative low sum borrows one from the high word, which
+  // high_word() gives back: both sums stay exact.
+  static __device__ __forceinline__ void add2(unsigned int* p, int lo, int hi) {
+    const unsigned long long v = ((unsigned long long)(unsigned)(hi + (lo >> 31)) << 32) | (unsigned)lo;
+    atomicAdd(reinterpret_cast<unsigned long long*>(p), v);
   }
   static __device__ __forceinline__ float value(unsigned int a, float inv, int) { return (float)(int)a * inv; }
 };
@@ -221,15 +231,30 @@ __device__ __forceinline__ AT* g_at(AT* gs, unsigned off) {
   return reinterpret_cast<AT*>(reinterpret_cast<char*>(gs) + off * (unsigned)(sizeof(AT) / 4));
 }
 
+// Whether tiles of two or more restarts keep their accumulator words in pairs.
+template <int MAXB, class AT>
+constexpr bool pair_words() {
+  return MAXB <= kMaxbShort && sizeof(AT) == 4;
+}
+
 // Where a pair's per-literal gradient terms go: the tile's fixed-point LDS
 // accumulator (GradSink), or a per-lane sum of squares (SquareSink, for the
 // per-constraint gradient statistics).
 // Terms of pad slots (code of a pad row, variable >= n) go to the pad row's
 // accumulator, which is never read; the statistics sink skips them.
-template <class AT>
+template <class AT, bool PAIR>
 struct GradSink {
   AT* gs;
-  __device__ __forceinline__ void add(unsigned off, float v, int) { FixedAcc<AT>::add(g_at(gs, off), v); }
+  bool low;  // PAIR: this lane's restart is the low word of a pair
+  __device__ __forceinline__ void add(unsigned off, float v, int) {
+    if constexpr (PAIR) {
+      if (low) {
+        FixedAcc<AT>::add2(g_at(gs, off), FixedAcc<AT>::round(v), 0);
+        return;
+      }
+    }
+    FixedAcc<AT>::add(g_at(gs, off), v);
+  }
 };
 struct SquareSink {
   float acc;
@@ -980,8 +1005,12 @@ __device__ __forceinline__ void prod_pair_r2(const Fetched<KMAX>& fp, int t2, in
       sb2 *= fb2[j];
     }
     AT* gp = g_at(gs, el[j]);
-    FixedAcc<AT>::add(gp, flip(ga, sg));
-    FixedAcc<AT>::add(gp + 1, flip(gb, sg));
+    if constexpr (sizeof(AT) == 4) {
+      FixedAcc<AT>::add2(gp, FixedAcc<AT>::round(flip(ga, sg)), FixedAcc<AT>::round(flip(gb, sg)));
+    } else {
+      FixedAcc<AT>::add(gp, flip(ga, sg));
+      FixedAcc<AT>::add(gp + 1, flip(gb, sg));
+    }
   }
 }
 
@@ -1186,7 +1215,7 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
         if (valid && lig == 0) atomicAdd(&so.acc[S.c_begin + b_u + sub], (unsigned long long)fixed_term(sq * so.scale));
       } else {
         if (valid) {
-          GradSink<AT> sk{gs};
+          GradSink<AT, pair_words<MAXB, AT>()> sk{gs, logT >= 1 && (t & 1) == 0};
           eval_pair(sk, fp);
         }
       }
@@ -1410,6 +1439,17 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
       if (eval) A.obj_out[r] = F;
     }
   };
+  // The accumulator of element i, this lane's (lane i mod 64): the high word of a
+  // pair takes back what its low word borrowed (the neighbouring lane holds it).
+  const bool paired = pair_words<MAXB, AT>() && logT >= 1;
+  auto grad_word = [&](int i) {
+    AT g = gs[i];
+    if constexpr (pair_words<MAXB, AT>()) {
+      const unsigned low = (unsigned)__builtin_amdgcn_update_dpp(0, (int)g, 0xA0, 0xf, 0xf, true);  // lanes 0,0,2,2
+      if (paired && (i & 1)) g += low >> 31;
+    }
+    return g;
+  };
   // Short-constraint variants take the objective of step s off the critical
   // path: its deposits and step s-1's finalize run at the start of step s + 1,
   // where the dynamic work claims absorb them (a wave that spends time there
@@ -1444,7 +1484,7 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
       if (A.g_out) {
         for (int i = tid; i < NT; i += nth) {
           const int v = i >> logT, tt = i & (T - 1);
-          A.g_out[(size_t)v * ldx + r0 + tt] = FixedAcc<AT>::value(gs[i], A.ginv, P.occ[v]);
+          A.g_out[(size_t)v * ldx + r0 + tt] = FixedAcc<AT>::value(grad_word(i), A.ginv, P.occ[v]);
         }
       }
     } else if (sizeof(AT) == 4 && A.tol <= 0.f && !A.fixed && (NT & 3) == 0) {
@@ -1455,7 +1495,11 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
       uint4* g4 = reinterpret_cast<uint4*>(gs);
       for (int i = tid; i < (NT >> 2); i += nth) {
         float4 x = x4[i];
-        const uint4 g = g4[i];
+        uint4 g = g4[i];
+        if constexpr (pair_words<MAXB, AT>()) {
+          g.y += __builtin_amdgcn_ubfe(g.x, 31, paired ? 1 : 0);
+          g.w += __builtin_amdgcn_ubfe(g.z, 31, paired ? 1 : 0);
+        }
         x.x = fminf(1.f, fmaxf(-1.f, fmaf(-lr, (float)(int)g.x * ginv, x.x)));
         x.y = fminf(1.f, fmaxf(-1.f, fmaf(-lr, (float)(int)g.y * ginv, x.y)));
         x.z = fminf(1.f, fmaxf(-1.f, fmaf(-lr, (float)(int)g.z * ginv, x.z)));
@@ -1468,7 +1512,7 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
       float dmax = 0.f;  // this thread's elements all belong to restart t (nth is a multiple of T)
       for (int i = tid; i < NT; i += nth) {
         const int v = i >> logT;
-        float xn = fmaf(-lr, FixedAcc<AT>::value(gs[i], A.ginv, P.occ[v]), xs[i]);
+        float xn = fmaf(-lr, FixedAcc<AT>::value(grad_word(i), A.ginv, P.occ[v]), xs[i]);
         xn = fminf(1.f, fmaxf(-1.f, xn));
         if (A.fixed && A.fixed[v] != 0) xn = (float)A.fixed[v];
         dmax = fmaxf(dmax, fabsf(xn - xs[i]));
