@@ -205,7 +205,9 @@ __device__ __forceinline__ void fetch_pair(const ProblemDev& P, const Segment& S
 #pragma unroll
   for (int j = 0; j < J; ++j) f.code[j] = __builtin_amdgcn_raw_buffer_load_b32(rs, voff, j * S.c_count * 4, 0);
   const int c = S.c_begin + cl;
-  if constexpr (KIND != KIND_PMF)
+  if constexpr (KIND != KIND_PMF && KMAX <= 8)
+    f.cls = S.par_fixed != 0 ? S.par_fixed : P.c_par[c];
+  else if constexpr (KIND != KIND_PMF)
     f.cls = P.c_par[c];
   else
     f.cls = S.cls_fixed >= 0 ? S.cls_fixed : P.c_cls[c];
@@ -989,6 +991,25 @@ __device__ __forceinline__ void prod_pair_r2(const Fetched<KMAX>& fp, int t2, in
     fcb = fmaf(fp.w, feb, fcb);
     s1 *= fp.w;
     s2 *= fp.w;
+  }
+  if constexpr (UW && NN == 1 && J == 3) {
+    // Three literals, unit weight: the scale is a power of two, so the literal's
+    // sign goes onto it once for both restarts and scaling last rounds the same
+    // (one sign flip less per restart and literal than below).
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const int p = j == 0 ? 1 : 0, q = j == 2 ? 1 : 2;
+      const float sj = flip(s1, lit_sign(fp.code[j]));
+      const float ga = sj * (fa1[p] * fa1[q]), gb = sj * (fb1[p] * fb1[q]);
+      AT* gp = g_at(gs, el[j]);
+      if constexpr (sizeof(AT) == 4) {
+        FixedAcc<AT>::add2(gp, FixedAcc<AT>::round(ga), FixedAcc<AT>::round(gb));
+      } else {
+        FixedAcc<AT>::add(gp, ga);
+        FixedAcc<AT>::add(gp + 1, gb);
+      }
+    }
+    return;
   }
   // the suffix products start at the gradient scales (one product per term)
   float sa1 = s1, sb1 = s1, sa2 = s2, sb2 = s2;
