@@ -43,7 +43,8 @@ def objects():
     for maxb in ("kMaxbAll", "kMaxbMid", "kMaxbShort"):
         for bits, acc in ((32, "unsigned int"), (64, "unsigned long long")):
             flags = [f"-DPCLS_VARIANT_MAXB={maxb}", f"-DPCLS_VARIANT_ACC={acc}"]
-            out.append((f"pcls_{maxb}_{bits}.o", "pcls.hip", flags + (["-DPCLS_VARIANT_STATS"] if bits == 32 else [])))
+            out.append((f"pcls_{maxb}_{bits}.o", "pcls.hip", flags + (["-DPCLS_VARIANT_STATS"] if bits == 32 else [])
+                        + (["-DPCLS_VARIANT_SMALL"] if maxb == "kMaxbShort" else [])))
     return out + [(src.rsplit(".", 1)[0] + ".o", src, []) for src in SOURCES]
 
 

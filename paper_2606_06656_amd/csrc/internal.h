@@ -141,9 +141,10 @@ struct ProblemDev {
                                  // bit 31 set for a negated literal; a slot past the constraint's
                                  // end codes a pad row (variable >= n)
   const int32_t* c_cls;          // per constraint class
+  int32_t n_codes;               // entries of litT
   const int32_t* c_par;          // per constraint of a product kind: two bf16 values, PROD1 b and c1,
                                  // PROD2 c2 and c1 (high and low half); of a DFT one: its class's
-                                 // node table entry
+                                 // node table entry; of a PMF one: its class
   const float* c_w;              // per constraint weight
   const int32_t* row_ptr;        // planned-order CSR (extract / streaming engine)
   const int32_t* lit;            // planned-order literal codes

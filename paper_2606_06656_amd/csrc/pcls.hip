@@ -10,6 +10,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstdlib>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -210,8 +211,31 @@ __device__ __forceinline__ void fetch_pair(const ProblemDev& P, const Segment& S
   else if constexpr (KIND != KIND_PMF)
     f.cls = P.c_par[c];
   else
-    f.cls = S.cls_fixed >= 0 ? S.cls_fixed : P.c_cls[c];
+    f.cls = S.cls_fixed >= 0 ? S.cls_fixed : P.c_par[c];
   f.w = P.unit_weights ? 1.f : P.c_w[c];
+}
+
+// The constraints' codes, parameters and weights in LDS, and the wave's place
+// (small problems, see tile_kernel).
+struct LdsCodes {
+  const int* lit;
+  const int* par;
+  const float* w;
+  int wave, waves;  // waves: a power of two
+  int turn;         // chunks dealt so far, over the segments of a step
+  bool worked;      // this wave has had a chunk in this step
+};
+
+template <int KIND, int J>
+__device__ __forceinline__ void fetch_lds(const ProblemDev& P, const Segment& S, const LdsCodes& L, int c_local, int lig,
+                                          Fetched<J>& f) {
+  const int cl = min(c_local, S.c_count - 1);
+#pragma unroll
+  for (int j = 0; j < J; ++j) f.code[j] = L.lit[S.lit_base + (lig * J + j) * S.c_count + cl];
+  const int fixed = KIND == KIND_PMF ? S.cls_fixed : S.par_fixed;
+  const bool uni = KIND == KIND_PMF ? fixed >= 0 : (KIND != KIND_DFT && fixed != 0);
+  f.cls = uni ? fixed : L.par[S.c_begin + cl];
+  f.w = P.unit_weights ? 1.f : L.w[S.c_begin + cl];
 }
 
 // Literal decode: LDS element of (variable, restart t) and the sign bit, which
@@ -1091,6 +1115,20 @@ __device__ __forceinline__ void run_chunks(int count, CLAIM claim, FETCH fetch, 
   }
 }
 
+// The same with the codes in LDS: chunks of one pair a lane are dealt to the waves
+// in turn (each segment goes on where the last one stopped), without claims.
+template <class F, class FETCH, class EVAL>
+__device__ __forceinline__ void deal_chunks(int count, int per_wave, LdsCodes& L, FETCH fetch, EVAL eval) {
+  const int first = (L.wave - L.turn) & (L.waves - 1);
+  for (int base = first * per_wave; base < count; base += L.waves * per_wave) {
+    F f;
+    fetch(base, f);
+    eval(base, f);
+  }
+  L.turn += (count + per_wave - 1) >> (31 - __builtin_clz(per_wave));
+  L.worked |= first * per_wave < count;
+}
+
 // The two-restarts-per-lane variant of run_segment for short product kinds.
 template <int KIND, int KMAX, bool UW, class AT>
 __device__ __forceinline__ void run_segment_r2(const ProblemDev& P, const Segment& S, const float* xs, AT* gs,
@@ -1140,12 +1178,12 @@ struct StatsOut {
   float scale;
 };
 
-template <int KIND, int KMAX, int MAXB, class AT, bool ST = false>
+template <int KIND, int KMAX, int MAXB, class AT, bool ST = false, bool CL = false>
 __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& S, const float* xs, AT* gs,
                                             ObjAcc& facc, float gsc, float fsc, int tid, int logT, int* ctr,
-                                            StatsOut so = {}) {
+                                            LdsCodes& L, StatsOut so = {}) {
   if constexpr (!ST && (KIND == KIND_PROD1 || KIND == KIND_PROD2) && MAXB <= kMaxbShort && KMAX <= 8) {
-    if (logT >= 1) {
+    if (!CL && logT >= 1) {
       // unit weights (a problem-wide flag): no weight fetch or multiply
       if (P.unit_weights)
         run_segment_r2<KIND, KMAX, true>(P, S, xs, gs, facc, gsc, fsc, tid, logT, ctr);
@@ -1157,7 +1195,7 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
   constexpr int G = group_size(KIND, KMAX);
   constexpr int LG = Log2<G>::v;
   constexpr int J = KMAX / G;
-  constexpr int U = pairs_per_lane<KIND, J, MAXB>();
+  constexpr int U = CL ? 1 : pairs_per_lane<KIND, J, MAXB>();
   // keep the lane-index arithmetic inside the segment: hoisting it out of the
   // step loop for every instantiation at once exhausts the register budget
   asm volatile("" : "+v"(tid));
@@ -1173,7 +1211,12 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
   };
   auto fetch = [&](int b, FetchedU<J, U>& f) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) fetch_pair<KIND, J, KMAX>(P, S, b + u * per_wave + sub, lig, f.p[u]);
+    for (int u = 0; u < U; ++u) {
+      if constexpr (CL)
+        fetch_lds<KIND, J>(P, S, L, b + sub, lig, f.p[u]);
+      else
+        fetch_pair<KIND, J, KMAX>(P, S, b + u * per_wave + sub, lig, f.p[u]);
+    }
   };
   auto eval = [&](int base, const FetchedU<J, U>& cur) {
     // A chunk (aligned, fixed pairs per lane, fixed order) sums its objective
@@ -1244,7 +1287,10 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
     facc.own += fixed_term(fchunk);
   };
   constexpr bool kHeavy = KIND == KIND_DFT || (KIND == KIND_PMF && KMAX > 8);
-  run_chunks<kHeavy, FetchedU<J, U>>(S.c_count, claim, fetch, eval);
+  if constexpr (CL)
+    deal_chunks<FetchedU<J, U>>(S.c_count, per_wave, L, fetch, eval);
+  else
+    run_chunks<kHeavy, FetchedU<J, U>>(S.c_count, claim, fetch, eval);
 }
 
 #define PCLS_BUCKET_CASES(KIND, X) \
@@ -1287,13 +1333,13 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
 
 #define PCLS_CASE(KIND, B, KMAX)                                                                    \
   case (KIND)*kNumBuckets + (B):                                                                    \
-    if constexpr ((B) <= MAXB) run_segment<KIND, KMAX, MAXB, AT, ST>(P, S, xs, gs, facc, gsc, fsc, tid, logT, ctr, so); \
+    if constexpr ((B) <= MAXB) run_segment<KIND, KMAX, MAXB, AT, ST, CL>(P, S, xs, gs, facc, gsc, fsc, tid, logT, ctr, L, so); \
     break;
 
-template <int MAXB, class AT, bool ST = false>
+template <int MAXB, class AT, bool ST = false, bool CL = false>
 __device__ __forceinline__ void run_any_segment(const ProblemDev& P, const Segment& S, const float* xs, AT* gs,
                                                 ObjAcc& facc, float gsc, float fsc, int tid, int logT,
-                                                int* ctr, StatsOut so = {}) {
+                                                int* ctr, LdsCodes& L, StatsOut so = {}) {
   switch (S.kind * kNumBuckets + S.bucket) {
     PCLS_BUCKET_CASES(KIND_PROD1, PCLS_CASE)
     PCLS_BUCKET_CASES(KIND_PROD2, PCLS_CASE)
@@ -1361,15 +1407,21 @@ __device__ __forceinline__ unsigned long long take_slots(unsigned long long* sl,
   return (a[0] + a[1]) + (a[2] + a[3]);
 }
 
+__device__ __forceinline__ Segment load_segment(const ProblemDev& P, int sg) {
+  kptr<Segment> S = kconst(P.segments) + sg;
+  return {S->kind, S->bucket, S->c_begin, S->c_count, S->lit_base, S->par_fixed, S->cls_fixed, S->m_max, S->z_off};
+}
+
 // All n_steps steps of one tile with its state in LDS.
 // LDS: x[n][T] float | g[n][T] fixed point | two slot sets for the objective
 //      (64-bit fixed point; per set 64 slots, and 2 x 64 more for the even and
 //      odd restarts of two-restart lanes when T >= 2; the long-constraint
 //      variants use slot t of set 0 for restart t) |
-//      one work counter per segment | per restart: converged flag, max |dx|.
-template <int MAXB, class AT>
+//      one work counter per segment | per restart: converged flag, max |dx| |
+//      CL: literal codes, one word a constraint, weights unless all 1.
+template <int MAXB, class AT, bool CL = false>
 __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArgs& A, unsigned long long* lds_raw) {
-  const int logT = A.logT;
+  const int logT = CL ? 0 : A.logT;
   const int T = 1 << logT;
   const int NT = P.n << logT;                 // state elements stepped
   const int NR = (P.n + P.n_pad) << logT;     // with the pad rows
@@ -1384,8 +1436,12 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
   const int tid = threadIdx.x, nth = blockDim.x;
   const int r0 = A.r0, ldx = A.ldx;
   const int t = tid & (T - 1);
-  const bool eval = A.obj_out != nullptr;
+  const bool eval = !CL && A.obj_out != nullptr;
   const int n_seg = P.n_segments;
+  // the thread that finishes restart r0 + ot: one of the first T, or (CL) one of the
+  // last wave, which the chunks reach last
+  const bool owner = CL ? tid == nth - kWave : tid < T;
+  const int ot = CL ? 0 : tid;
 
   for (int i = tid; i < NT; i += nth) {
     const int v = i >> logT, tt = i & (T - 1);
@@ -1404,6 +1460,18 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
     dxmax[tid] = 0u;
   }
   if (tid < n_seg) ctr[tid] = 0;
+  LdsCodes L{};
+  if constexpr (CL) {
+    int* lit = reinterpret_cast<int*>(dxmax + T);
+    int* par = lit + P.n_codes;
+    float* w = reinterpret_cast<float*>(par + P.m);
+    for (int i = tid; i < P.n_codes; i += nth) lit[i] = P.litT[i];
+    for (int i = tid; i < P.m; i += nth) {
+      par[i] = P.c_par[i];
+      if (!P.unit_weights) w[i] = P.c_w[i];
+    }
+    L = {lit, par, w, __builtin_amdgcn_readfirstlane(tid >> 6), nth >> 6, 0};
+  }
   __syncthreads();
   float F_last = 0.f;  // threads tid < T: last evaluated objective of restart r0 + tid
 
@@ -1444,8 +1512,8 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
     // each slot has one reader, which clears it for the step after next
     unsigned long long acc;
     if constexpr (MAXB <= kMaxbShort) {
-      int q = t;
-      asm volatile("" : "+v"(q));
+      int q = CL ? 0 : t;
+      if constexpr (!CL) asm volatile("" : "+v"(q));
       acc = take_slots(sl, q, T);
       if (logT >= 1) acc += take_slots(sl + ((q & 1) ? 2 * kWave : kWave), q >> 1, T >> 1);
     } else {
@@ -1453,7 +1521,7 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
       sl[t] = 0ull;
     }
     const float F = FixedAcc<unsigned long long>::value_exact(acc, A.finv) + P.f_const;
-    const int r = r0 + tid;
+    const int r = r0 + ot;
     F_last = F;
     if (r < A.R) {
       if (A.trace) A.trace[(size_t)step * A.R + r] = F;
@@ -1479,25 +1547,38 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
   ObjAcc prev{0, 0, 0};
   int done = A.n_steps;  // steps taken (fewer once every restart has converged)
 
+  Segment S0{};
+  if constexpr (CL) {
+    if (n_seg > 0) S0 = load_segment(P, 0);  // of the only segment, most of the time: kept over the steps
+  }
   for (int s = 0; s < A.n_steps; ++s) {
     if constexpr (kDefer) {
       if (s > 0) {
-        deposit(prev, set_of(s - 1));
-        if (s > 1 && tid < T) finalize(s - 2, set_of(s - 2));
+        if (!CL || L.worked) deposit(prev, set_of(s - 1));
+        if (s > 1 && owner) finalize(s - 2, set_of(s - 2));
       }
     }
     ObjAcc facc{0, 0, 0};
-    kptr<Segment> segs = kconst(P.segments);
-    for (int sg = 0; sg < n_seg; ++sg) {
-      const Segment S{segs[sg].kind,    segs[sg].bucket, segs[sg].c_begin,   segs[sg].c_count,
-                      segs[sg].lit_base, segs[sg].par_fixed, segs[sg].cls_fixed, segs[sg].m_max, segs[sg].z_off};
-      run_any_segment<MAXB>(P, S, xs, gs, facc, A.gsc, A.fsc, tid, logT, ctr + sg);
+    if constexpr (CL) {
+      L.turn = 0;
+      L.worked = false;
+      for (int sg = 0; sg < n_seg; ++sg) {
+        const Segment S = sg == 0 ? S0 : load_segment(P, sg);
+        run_any_segment<MAXB, AT, false, CL>(P, S, xs, gs, facc, A.gsc, A.fsc, tid, logT, nullptr, L);
+      }
+    } else {
+      for (int sg = 0; sg < n_seg; ++sg) {
+        const Segment S = load_segment(P, sg);
+        run_any_segment<MAXB, AT, false, CL>(P, S, xs, gs, facc, A.gsc, A.fsc, tid, logT, ctr + sg, L);
+      }
     }
     if constexpr (!kDefer) deposit(facc, set_of(0));
     __syncthreads();
-    if (tid < n_seg) ctr[tid] = 0;  // every wave has left the segment loops
+    if constexpr (!CL) {
+      if (tid < n_seg) ctr[tid] = 0;  // every wave has left the segment loops
+    }
     if constexpr (!kDefer) {
-      if (tid < T) finalize(s, set_of(0));
+      if (owner) finalize(s, set_of(0));
     } else {
       prev = facc;
     }
@@ -1548,13 +1629,13 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
     __syncthreads();
     if (!eval && A.tol > 0.f) {
       // convergence: a tile stops once every restart in it has converged
-      if (tid < T) {
-        const int r = r0 + tid;
-        if (!conv[tid] && __uint_as_float(dxmax[tid]) < A.tol) {
-          conv[tid] = 1;
+      if (owner) {
+        const int r = r0 + ot;
+        if (!conv[ot] && __uint_as_float(dxmax[ot]) < A.tol) {
+          conv[ot] = 1;
           if (A.iters && r < A.R) A.iters[r] = s + 1;
         }
-        dxmax[tid] = 0u;
+        dxmax[ot] = 0u;
       }
       __syncthreads();
       int all = 1;
@@ -1568,16 +1649,16 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
   }
   if constexpr (kDefer) {
     if (done > 0) {
-      deposit(prev, set_of(done - 1));
-      if (done > 1 && tid < T) finalize(done - 2, set_of(done - 2));
+      if (!CL || L.worked) deposit(prev, set_of(done - 1));
+      if (done > 1 && owner) finalize(done - 2, set_of(done - 2));
       __syncthreads();
-      if (tid < T) finalize(done - 1, set_of(done - 1));
+      if (owner) finalize(done - 1, set_of(done - 1));
     }
   }
   // a tile that stopped early repeats its last objective for the remaining steps
-  if (tid < T && A.trace && r0 + tid < A.R)
-    for (int q = done; q < A.n_steps; ++q) A.trace[(size_t)q * A.R + r0 + tid] = F_last;
-  if (!eval && A.tol > 0.f && A.iters && tid < T && r0 + tid < A.R && !conv[tid]) A.iters[r0 + tid] = A.n_steps;
+  if (owner && A.trace && r0 + ot < A.R)
+    for (int q = done; q < A.n_steps; ++q) A.trace[(size_t)q * A.R + r0 + ot] = F_last;
+  if (!eval && A.tol > 0.f && A.iters && owner && r0 + ot < A.R && !conv[ot]) A.iters[r0 + ot] = A.n_steps;
   if (!eval) {
     for (int i = tid; i < NT; i += nth) {
       const int v = i >> logT, tt = i & (T - 1);
@@ -1592,11 +1673,15 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
 // allocation covers its longest code path, so short-constraint problems run a
 // variant with fewer registers and more waves per SIMD) and by the width of the
 // fixed-point gradient accumulator (64-bit, or 32-bit where LDS is short).
-template <int MAXB, class AT>
+// CL: small problems, whose codes fit LDS next to the state and whose steps are a
+// few chunks a wave.  Such a step is a chain of latencies, not work: the claim, the
+// codes' way from L2, the gather, the atomics, two barriers.  Codes from LDS and
+// chunks dealt in turn take out the first two.
+template <int MAXB, class AT, bool CL>
 __global__ void __launch_bounds__(1024) tile_kernel(ProblemDev P, TileArgs A) {
   extern __shared__ __attribute__((aligned(16))) unsigned long long lds_raw[];  // 16 B: vector LDS accesses
   A.r0 = blockIdx.x << A.logT;
-  resident_tile<MAXB, AT>(P, A, lds_raw);
+  resident_tile<MAXB, AT, CL>(P, A, lds_raw);
 }
 
 // ---------------------------------------------------- constraint statistics
@@ -1615,11 +1700,10 @@ __global__ void __launch_bounds__(1024) stats_kernel(ProblemDev P, const float* 
   if ((int)threadIdx.x < P.n_segments) ctr[threadIdx.x] = 0;
   __syncthreads();
   ObjAcc facc{0, 0, 0};
-  kptr<Segment> segs = kconst(P.segments);
+  LdsCodes L{};
   for (int sg = 0; sg < P.n_segments; ++sg) {
-    const Segment S{segs[sg].kind,    segs[sg].bucket, segs[sg].c_begin,   segs[sg].c_count,
-                    segs[sg].lit_base, segs[sg].par_fixed, segs[sg].cls_fixed, segs[sg].m_max, segs[sg].z_off};
-    run_any_segment<MAXB, unsigned int, true>(P, S, xs, nullptr, facc, 1.f, 0.f, (int)threadIdx.x, 0, ctr + sg, so);
+    const Segment S = load_segment(P, sg);
+    run_any_segment<MAXB, unsigned int, true>(P, S, xs, nullptr, facc, 1.f, 0.f, (int)threadIdx.x, 0, ctr + sg, L, so);
   }
 }
 
@@ -1656,6 +1740,7 @@ __device__ __forceinline__ ProblemDev load_problem(kptr<BatchInst> bi) {
   P.litT = bi->P.litT;
   P.c_cls = bi->P.c_cls;
   P.c_par = bi->P.c_par;
+  P.n_codes = bi->P.n_codes;
   P.c_w = bi->P.c_w;
   P.row_ptr = bi->P.row_ptr;
   P.lit = bi->P.lit;
@@ -1707,7 +1792,10 @@ __global__ void __launch_bounds__(1024) batch_kernel(const BatchInst* __restrict
 
 #ifdef PCLS_VARIANT_MAXB
 
-template __global__ void tile_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC>(ProblemDev, TileArgs);
+template __global__ void tile_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC, false>(ProblemDev, TileArgs);
+#ifdef PCLS_VARIANT_SMALL
+template __global__ void tile_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC, true>(ProblemDev, TileArgs);
+#endif
 template __global__ void batch_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC>(const BatchInst*, const BatchItem*, int,
                                                                            unsigned int*, float, int, int);
 #ifdef PCLS_VARIANT_STATS
@@ -1720,8 +1808,8 @@ template __global__ void stats_kernel<PCLS_VARIANT_MAXB>(ProblemDev, const float
 #else
 
 #define PCLS_EXTERN_VARIANT(MAXB)                                                                                  \
-  extern template __global__ void tile_kernel<MAXB, unsigned int>(ProblemDev, TileArgs);                           \
-  extern template __global__ void tile_kernel<MAXB, unsigned long long>(ProblemDev, TileArgs);                     \
+  extern template __global__ void tile_kernel<MAXB, unsigned int, false>(ProblemDev, TileArgs);                    \
+  extern template __global__ void tile_kernel<MAXB, unsigned long long, false>(ProblemDev, TileArgs);              \
   extern template __global__ void batch_kernel<MAXB, unsigned int>(const BatchInst*, const BatchItem*, int,        \
                                                                    unsigned int*, float, int, int);                \
   extern template __global__ void batch_kernel<MAXB, unsigned long long>(const BatchInst*, const BatchItem*, int,  \
@@ -1730,6 +1818,8 @@ template __global__ void stats_kernel<PCLS_VARIANT_MAXB>(ProblemDev, const float
 PCLS_EXTERN_VARIANT(kMaxbShort)
 PCLS_EXTERN_VARIANT(kMaxbMid)
 PCLS_EXTERN_VARIANT(kMaxbAll)
+extern template __global__ void tile_kernel<kMaxbShort, unsigned int, true>(ProblemDev, TileArgs);
+extern template __global__ void tile_kernel<kMaxbShort, unsigned long long, true>(ProblemDev, TileArgs);
 
 }  // namespace engine
 }  // namespace pcls
@@ -2079,12 +2169,14 @@ int32_t device_limits(DeviceLimits& out) {
     d.n_cu = v;
   }
   if (!d.lds_attr_set) {
-    const void* variants[] = {(const void*)tile_kernel<kMaxbShort, unsigned long long>,
-                              (const void*)tile_kernel<kMaxbMid, unsigned long long>,
-                              (const void*)tile_kernel<kMaxbAll, unsigned long long>,
-                              (const void*)tile_kernel<kMaxbShort, unsigned int>,
-                              (const void*)tile_kernel<kMaxbMid, unsigned int>,
-                              (const void*)tile_kernel<kMaxbAll, unsigned int>,
+    const void* variants[] = {(const void*)tile_kernel<kMaxbShort, unsigned long long, false>,
+                              (const void*)tile_kernel<kMaxbMid, unsigned long long, false>,
+                              (const void*)tile_kernel<kMaxbAll, unsigned long long, false>,
+                              (const void*)tile_kernel<kMaxbShort, unsigned int, false>,
+                              (const void*)tile_kernel<kMaxbMid, unsigned int, false>,
+                              (const void*)tile_kernel<kMaxbAll, unsigned int, false>,
+                              (const void*)tile_kernel<kMaxbShort, unsigned int, true>,
+                              (const void*)tile_kernel<kMaxbShort, unsigned long long, true>,
                               (const void*)stats_kernel<kMaxbShort>,
                               (const void*)stats_kernel<kMaxbMid>,
                               (const void*)stats_kernel<kMaxbAll>};
@@ -2116,6 +2208,7 @@ struct Launch {
   int block;
   size_t lds;
   bool acc64;
+  bool small;  // codes in LDS (tile_kernel's CL)
 };
 
 // Restarts per workgroup: largest power of two whose state fits in LDS, at
@@ -2135,7 +2228,11 @@ bool auto_acc64(const pcls_problem* p, size_t cap) {
   return tile_lds_bytes(state_rows(p), std::max(1, p->tile_restarts), 8) <= cap;
 }
 
-int32_t choose_launch(const pcls_problem* p, int R, Launch& L) {
+constexpr int kSmallSteps = 2;
+const int kSmallChunks = getenv("KSC") ? atoi(getenv("KSC")) : 8;
+
+// steps: of the launch; 0 for an evaluation
+int32_t choose_launch(const pcls_problem* p, int R, int steps, Launch& L) {
   DeviceLimits lim;
   int32_t st = device_limits(lim);
   if (st != PCLS_OK) return st;
@@ -2167,14 +2264,22 @@ int32_t choose_launch(const pcls_problem* p, int R, Launch& L) {
     return set_error(PCLS_E_UNSUPPORTED,
                      "state of %d variables x %d restarts needs %zu bytes of LDS (device limit %d)", p->n, T, lds,
                      lim.lds_max);
+  // Small problems: codes in LDS where they fit and a wave gets at most kSmallChunks
+  // chunks a step.
+  const size_t lds_small = lds + 4 * (p->litT.size() + (size_t)p->m * (p->unit_weights ? 1 : 2));
+  const long long lanes = (long long)(p->L / 3 + 1) * T;
+  L.small = T == 1 && steps >= kSmallSteps && p->max_bucket <= kMaxbShort && lds_small <= cap && lanes <= 64LL * 16 * kSmallChunks;
   int block = p->block_threads;
-  if (block <= 0) block = (lds > cap / 2 || R_pad / T <= lim.n_cu) ? 1024 : 512;
+  if (block <= 0) {
+    block = (lds > cap / 2 || R_pad / T <= lim.n_cu) ? 1024 : 512;
+    if (L.small) block = 1024;
+  }
   if (block != 256 && block != 512 && block != 1024)
     return set_error(PCLS_E_INVALID, "block_threads %d must be 256, 512 or 1024", block);
   L.logT = 0;
   while ((1 << L.logT) < T) ++L.logT;
   L.block = block;
-  L.lds = lds;
+  L.lds = L.small ? lds_small : lds;
   L.acc64 = acc64;
   return PCLS_OK;
 }
@@ -2188,7 +2293,7 @@ int32_t check_bound(const pcls_problem* p) {
 int32_t launch_tile(const pcls_problem* p, int R, float* d_x, float lr, int n_steps, float* trace, float* obj,
                     float* grad, hipStream_t stream, const pcls_step_options* opt = nullptr) {
   Launch L;
-  int32_t st = choose_launch(p, R, L);
+  int32_t st = choose_launch(p, R, obj ? 0 : n_steps, L);
   if (st != PCLS_OK) return st;
   const int R_pad = round_up64(R);
   const int tiles = (R + (1 << L.logT) - 1) >> L.logT;  // padding-only tiles are skipped
@@ -2212,14 +2317,16 @@ int32_t launch_tile(const pcls_problem* p, int R, float* d_x, float lr, int n_st
   A.tol = opt ? opt->tol : 0.f;
   A.iters = opt ? opt->d_iters : nullptr;
   void (*kern)(ProblemDev, TileArgs);
-  if (L.acc64) {
-    kern = p->max_bucket <= kMaxbShort ? tile_kernel<kMaxbShort, unsigned long long>
-           : p->max_bucket <= kMaxbMid ? tile_kernel<kMaxbMid, unsigned long long>
-                                       : tile_kernel<kMaxbAll, unsigned long long>;
+  if (L.small) {
+    kern = L.acc64 ? tile_kernel<kMaxbShort, unsigned long long, true> : tile_kernel<kMaxbShort, unsigned int, true>;
+  } else if (L.acc64) {
+    kern = p->max_bucket <= kMaxbShort ? tile_kernel<kMaxbShort, unsigned long long, false>
+           : p->max_bucket <= kMaxbMid ? tile_kernel<kMaxbMid, unsigned long long, false>
+                                       : tile_kernel<kMaxbAll, unsigned long long, false>;
   } else {
-    kern = p->max_bucket <= kMaxbShort ? tile_kernel<kMaxbShort, unsigned int>
-           : p->max_bucket <= kMaxbMid ? tile_kernel<kMaxbMid, unsigned int>
-                                       : tile_kernel<kMaxbAll, unsigned int>;
+    kern = p->max_bucket <= kMaxbShort ? tile_kernel<kMaxbShort, unsigned int, false>
+           : p->max_bucket <= kMaxbMid ? tile_kernel<kMaxbMid, unsigned int, false>
+                                       : tile_kernel<kMaxbAll, unsigned int, false>;
   }
   hipLaunchKernelGGL(kern, dim3(tiles), dim3(L.block), L.lds, stream, p->dev, A);
   PCLS_HIP(hipGetLastError(), "tile_kernel launch");
@@ -2538,6 +2645,7 @@ int32_t pcls_upload(pcls_problem* p, void* d_ws, size_t bytes, void* stream) {
   D.sp = (const int8_t*)(b + p->off_sp);
   D.litT = (const int32_t*)(b + p->off_litT);
   D.c_cls = (const int32_t*)(b + p->off_ccls);
+  D.n_codes = (int32_t)p->litT.size();
   D.c_par = (const int32_t*)(b + p->off_cpar);
   D.c_w = (const float*)(b + p->off_cw);
   D.row_ptr = (const int32_t*)(b + p->off_rowptr);
@@ -2711,7 +2819,7 @@ int32_t pcls_launch_info(const pcls_problem* p, int32_t R, int32_t* tile_restart
   if (!p) return set_error(PCLS_E_INVALID, "problem handle is NULL");
   if (R < 1) return set_error(PCLS_E_INVALID, "R must be >= 1");
   Launch L;
-  int32_t st = choose_launch(p, R, L);
+  int32_t st = choose_launch(p, R, 1 << 30, L);
   if (st != PCLS_OK) return st;
   if (tile_restarts) *tile_restarts = 1 << L.logT;
   if (block_threads) *block_threads = L.block;

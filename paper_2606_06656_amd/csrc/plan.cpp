@@ -594,7 +594,10 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
         if (P->c_par[e] != S.par_fixed) S.par_fixed = 0;
       }
       if (C.kind == KIND_DFT) P->c_par[e] = C.node_off;
-      if (C.kind == KIND_PMF) S.m_max = std::max(S.m_max, C.window);
+      if (C.kind == KIND_PMF) {
+        S.m_max = std::max(S.m_max, C.window);
+        P->c_par[e] = P->c_cls[e];
+      }
       ++e;
     }
     S.c_count = e - j;
