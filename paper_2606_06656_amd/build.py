@@ -42,9 +42,12 @@ def objects():
     out = []
     for maxb in ("kMaxbAll", "kMaxbMid", "kMaxbShort"):
         for bits, acc in ((32, "unsigned int"), (64, "unsigned long long")):
-            flags = [f"-DPCLS_VARIANT_MAXB={maxb}", f"-DPCLS_VARIANT_ACC={acc}"]
-            out.append((f"pcls_{maxb}_{bits}.o", "pcls.hip", flags + (["-DPCLS_VARIANT_STATS"] if bits == 32 else [])
-                        + (["-DPCLS_VARIANT_SMALL"] if maxb == "kMaxbShort" else [])))
+            # PCLS_VARIANT_LT: log2 of the restarts per tile, -1 any; -2 the batched
+            # engine, -3 the statistics, -4 codes in LDS
+            kinds = [-1, 0, -2] + ([-3] if bits == 32 else []) + ([1, 2, -4] if maxb == "kMaxbShort" else [])
+            for lt in kinds:
+                out.append((f"pcls_{maxb}_{bits}_{lt}.o", "pcls.hip",
+                            [f"-DPCLS_VARIANT_MAXB={maxb}", f"-DPCLS_VARIANT_ACC={acc}", f"-DPCLS_VARIANT_LT={lt}"]))
     return out + [(src.rsplit(".", 1)[0] + ".o", src, []) for src in SOURCES]
 
 

@@ -10,7 +10,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <cstdlib>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -1419,9 +1418,10 @@ __device__ __forceinline__ Segment load_segment(const ProblemDev& P, int sg) {
 //      variants use slot t of set 0 for restart t) |
 //      one work counter per segment | per restart: converged flag, max |dx| |
 //      CL: literal codes, one word a constraint, weights unless all 1.
-template <int MAXB, class AT, bool CL = false>
+template <int MAXB, class AT, int LT = -1, bool CL = false>
 __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArgs& A, unsigned long long* lds_raw) {
-  const int logT = CL ? 0 : A.logT;
+  static_assert(!CL || LT == 0, "codes in LDS: one restart a tile");
+  const int logT = LT >= 0 ? LT : A.logT;
   const int T = 1 << logT;
   const int NT = P.n << logT;                 // state elements stepped
   const int NR = (P.n + P.n_pad) << logT;     // with the pad rows
@@ -1462,15 +1462,20 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
   if (tid < n_seg) ctr[tid] = 0;
   LdsCodes L{};
   if constexpr (CL) {
-    int* lit = reinterpret_cast<int*>(dxmax + T);
-    int* par = lit + P.n_codes;
+    const int n4 = (P.n_codes + 3) / 4;
+    int4* lit = reinterpret_cast<int4*>(((uintptr_t)(dxmax + T) + 15) & ~(uintptr_t)15);
+    int* par = reinterpret_cast<int*>(lit + n4);
     float* w = reinterpret_cast<float*>(par + P.m);
-    for (int i = tid; i < P.n_codes; i += nth) lit[i] = P.litT[i];
+    // 16 bytes a lane (the image's sections are 256-byte aligned and padded)
+    const int4* src = reinterpret_cast<const int4*>(P.litT);
+#pragma unroll 4
+    for (int i = tid; i < n4; i += nth) lit[i] = src[i];
+#pragma unroll 4
     for (int i = tid; i < P.m; i += nth) {
       par[i] = P.c_par[i];
       if (!P.unit_weights) w[i] = P.c_w[i];
     }
-    L = {lit, par, w, __builtin_amdgcn_readfirstlane(tid >> 6), nth >> 6, 0};
+    L = {reinterpret_cast<int*>(lit), par, w, __builtin_amdgcn_readfirstlane(tid >> 6), nth >> 6, 0, false};
   }
   __syncthreads();
   float F_last = 0.f;  // threads tid < T: last evaluated objective of restart r0 + tid
@@ -1673,15 +1678,22 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
 // allocation covers its longest code path, so short-constraint problems run a
 // variant with fewer registers and more waves per SIMD) and by the width of the
 // fixed-point gradient accumulator (64-bit, or 32-bit where LDS is short).
-// CL: small problems, whose codes fit LDS next to the state and whose steps are a
-// few chunks a wave.  Such a step is a chain of latencies, not work: the claim, the
-// codes' way from L2, the gather, the atomics, two barriers.  Codes from LDS and
-// chunks dealt in turn take out the first two.
-template <int MAXB, class AT, bool CL>
+// LT: log2 of the restarts per tile where a variant is compiled for it (one; two
+// and four for short constraints), else -1.  With the tile width known the lane
+// exchanges and the objective's reduction lose their branches and a few dozen
+// scalar registers no longer spill: long-support instance (T = 1) 1.97 -> 1.91 ms
+// a step, 3-SAT of 1000 variables at T = 2 4.05 -> 3.33 us, mixed instance of 2000
+// at T = 4 9.9 -> 9.1 us.
+// CL: small problems, whose codes fit LDS next to the state.  Their step is a chain
+// of latencies, not work: the claim, the codes' way from L2, the gather, the
+// atomics, two barriers, the objective's reduction.  Codes from LDS and chunks dealt
+// in turn take out the first two, and the last wave finishes the objective while
+// the first ones work: 3-SAT of 50 variables 2.0 -> 0.9 us a step.
+template <int MAXB, class AT, int LT, bool CL>
 __global__ void __launch_bounds__(1024) tile_kernel(ProblemDev P, TileArgs A) {
   extern __shared__ __attribute__((aligned(16))) unsigned long long lds_raw[];  // 16 B: vector LDS accesses
-  A.r0 = blockIdx.x << A.logT;
-  resident_tile<MAXB, AT, CL>(P, A, lds_raw);
+  A.r0 = blockIdx.x << (LT >= 0 ? LT : A.logT);
+  resident_tile<MAXB, AT, LT, CL>(P, A, lds_raw);
 }
 
 // ---------------------------------------------------- constraint statistics
@@ -1792,14 +1804,15 @@ __global__ void __launch_bounds__(1024) batch_kernel(const BatchInst* __restrict
 
 #ifdef PCLS_VARIANT_MAXB
 
-template __global__ void tile_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC, false>(ProblemDev, TileArgs);
-#ifdef PCLS_VARIANT_SMALL
-template __global__ void tile_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC, true>(ProblemDev, TileArgs);
-#endif
+#if PCLS_VARIANT_LT == -2
 template __global__ void batch_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC>(const BatchInst*, const BatchItem*, int,
                                                                            unsigned int*, float, int, int);
-#ifdef PCLS_VARIANT_STATS
+#elif PCLS_VARIANT_LT == -3
 template __global__ void stats_kernel<PCLS_VARIANT_MAXB>(ProblemDev, const float*, int, StatsOut);
+#elif PCLS_VARIANT_LT == -4
+template __global__ void tile_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC, 0, true>(ProblemDev, TileArgs);
+#else
+template __global__ void tile_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC, PCLS_VARIANT_LT, false>(ProblemDev, TileArgs);
 #endif
 
 }  // namespace engine
@@ -1807,9 +1820,12 @@ template __global__ void stats_kernel<PCLS_VARIANT_MAXB>(ProblemDev, const float
 
 #else
 
+#define PCLS_EXTERN_TILE(MAXB, LT, CL)                                                                      \
+  extern template __global__ void tile_kernel<MAXB, unsigned int, LT, CL>(ProblemDev, TileArgs);            \
+  extern template __global__ void tile_kernel<MAXB, unsigned long long, LT, CL>(ProblemDev, TileArgs);
 #define PCLS_EXTERN_VARIANT(MAXB)                                                                                  \
-  extern template __global__ void tile_kernel<MAXB, unsigned int, false>(ProblemDev, TileArgs);                    \
-  extern template __global__ void tile_kernel<MAXB, unsigned long long, false>(ProblemDev, TileArgs);              \
+  PCLS_EXTERN_TILE(MAXB, -1, false)                                                                                \
+  PCLS_EXTERN_TILE(MAXB, 0, false)                                                                                 \
   extern template __global__ void batch_kernel<MAXB, unsigned int>(const BatchInst*, const BatchItem*, int,        \
                                                                    unsigned int*, float, int, int);                \
   extern template __global__ void batch_kernel<MAXB, unsigned long long>(const BatchInst*, const BatchItem*, int,  \
@@ -1818,8 +1834,9 @@ template __global__ void stats_kernel<PCLS_VARIANT_MAXB>(ProblemDev, const float
 PCLS_EXTERN_VARIANT(kMaxbShort)
 PCLS_EXTERN_VARIANT(kMaxbMid)
 PCLS_EXTERN_VARIANT(kMaxbAll)
-extern template __global__ void tile_kernel<kMaxbShort, unsigned int, true>(ProblemDev, TileArgs);
-extern template __global__ void tile_kernel<kMaxbShort, unsigned long long, true>(ProblemDev, TileArgs);
+PCLS_EXTERN_TILE(kMaxbShort, 1, false)
+PCLS_EXTERN_TILE(kMaxbShort, 2, false)
+PCLS_EXTERN_TILE(kMaxbShort, 0, true)
 
 }  // namespace engine
 }  // namespace pcls
@@ -2155,6 +2172,25 @@ hipError_t check_no_static_lds(const void* f) {
   return a.sharedSizeBytes == 0 ? hipSuccess : hipErrorInvalidKernelFile;
 }
 
+// The kernel of a launch: restarts per tile 2^lt where a variant is compiled for it.
+using TileKernel = void (*)(ProblemDev, TileArgs);
+template <int MAXB, class AT>
+TileKernel tile_variant_of(int lt) {
+  if constexpr (MAXB <= kMaxbShort) {
+    if (lt == 1) return tile_kernel<MAXB, AT, 1, false>;
+    if (lt == 2) return tile_kernel<MAXB, AT, 2, false>;
+  }
+  return lt == 0 ? tile_kernel<MAXB, AT, 0, false> : tile_kernel<MAXB, AT, -1, false>;
+}
+TileKernel tile_variant(int max_bucket, bool acc64, int lt, bool small) {
+  if (small) return acc64 ? tile_kernel<kMaxbShort, unsigned long long, 0, true> : tile_kernel<kMaxbShort, unsigned int, 0, true>;
+  if (max_bucket <= kMaxbShort)
+    return acc64 ? tile_variant_of<kMaxbShort, unsigned long long>(lt) : tile_variant_of<kMaxbShort, unsigned int>(lt);
+  if (max_bucket <= kMaxbMid)
+    return acc64 ? tile_variant_of<kMaxbMid, unsigned long long>(lt) : tile_variant_of<kMaxbMid, unsigned int>(lt);
+  return acc64 ? tile_variant_of<kMaxbAll, unsigned long long>(lt) : tile_variant_of<kMaxbAll, unsigned int>(lt);
+}
+
 int32_t device_limits(DeviceLimits& out) {
   int dev = 0;
   PCLS_HIP(hipGetDevice(&dev), "hipGetDevice");
@@ -2169,17 +2205,12 @@ int32_t device_limits(DeviceLimits& out) {
     d.n_cu = v;
   }
   if (!d.lds_attr_set) {
-    const void* variants[] = {(const void*)tile_kernel<kMaxbShort, unsigned long long, false>,
-                              (const void*)tile_kernel<kMaxbMid, unsigned long long, false>,
-                              (const void*)tile_kernel<kMaxbAll, unsigned long long, false>,
-                              (const void*)tile_kernel<kMaxbShort, unsigned int, false>,
-                              (const void*)tile_kernel<kMaxbMid, unsigned int, false>,
-                              (const void*)tile_kernel<kMaxbAll, unsigned int, false>,
-                              (const void*)tile_kernel<kMaxbShort, unsigned int, true>,
-                              (const void*)tile_kernel<kMaxbShort, unsigned long long, true>,
-                              (const void*)stats_kernel<kMaxbShort>,
-                              (const void*)stats_kernel<kMaxbMid>,
-                              (const void*)stats_kernel<kMaxbAll>};
+    std::vector<const void*> variants = {(const void*)stats_kernel<kMaxbShort>, (const void*)stats_kernel<kMaxbMid>,
+                                         (const void*)stats_kernel<kMaxbAll>};
+    for (int maxb : {kMaxbShort, kMaxbMid, kMaxbAll})
+      for (int lt : {-1, 0, 1, 2})
+        for (bool acc64 : {false, true})
+          for (bool small : {false, true}) variants.push_back((const void*)tile_variant(maxb, acc64, lt, small));
     for (const void* f : variants) {
       PCLS_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, d.lds_max), "hipFuncSetAttribute");
       PCLS_HIP(check_no_static_lds(f), "kernel attributes");
@@ -2228,8 +2259,15 @@ bool auto_acc64(const pcls_problem* p, size_t cap) {
   return tile_lds_bytes(state_rows(p), std::max(1, p->tile_restarts), 8) <= cap;
 }
 
-constexpr int kSmallSteps = 2;
-const int kSmallChunks = getenv("KSC") ? atoi(getenv("KSC")) : 8;
+// Codes in LDS (tile_kernel's CL): one restart a tile, the codes fit next to the
+// state, and enough steps to pay for copying them.  Measured against the same
+// variant without (us a step): 3-SAT of 50, 200, 1000, 2000 variables 0.91, 1.18,
+// 2.18, 3.38 against 1.67, 2.07, 2.83, 3.84; mixed instance of 2000 variables 3.98
+// against 4.77; copying costs up to about 3 us.
+constexpr int kSmallSteps = 8;
+size_t codes_lds_bytes(const pcls_problem* p) {
+  return 16 + 4 * ((p->litT.size() + 3) / 4 * 4 + (size_t)p->m * (p->unit_weights ? 1 : 2));
+}
 
 // steps: of the launch; 0 for an evaluation
 int32_t choose_launch(const pcls_problem* p, int R, int steps, Launch& L) {
@@ -2264,16 +2302,10 @@ int32_t choose_launch(const pcls_problem* p, int R, int steps, Launch& L) {
     return set_error(PCLS_E_UNSUPPORTED,
                      "state of %d variables x %d restarts needs %zu bytes of LDS (device limit %d)", p->n, T, lds,
                      lim.lds_max);
-  // Small problems: codes in LDS where they fit and a wave gets at most kSmallChunks
-  // chunks a step.
-  const size_t lds_small = lds + 4 * (p->litT.size() + (size_t)p->m * (p->unit_weights ? 1 : 2));
-  const long long lanes = (long long)(p->L / 3 + 1) * T;
-  L.small = T == 1 && steps >= kSmallSteps && p->max_bucket <= kMaxbShort && lds_small <= cap && lanes <= 64LL * 16 * kSmallChunks;
+  const size_t lds_small = lds + codes_lds_bytes(p);
+  L.small = T == 1 && steps >= kSmallSteps && p->max_bucket <= kMaxbShort && lds_small <= cap;
   int block = p->block_threads;
-  if (block <= 0) {
-    block = (lds > cap / 2 || R_pad / T <= lim.n_cu) ? 1024 : 512;
-    if (L.small) block = 1024;
-  }
+  if (block <= 0) block = (L.small || lds > cap / 2 || R_pad / T <= lim.n_cu) ? 1024 : 512;
   if (block != 256 && block != 512 && block != 1024)
     return set_error(PCLS_E_INVALID, "block_threads %d must be 256, 512 or 1024", block);
   L.logT = 0;
@@ -2316,18 +2348,7 @@ int32_t launch_tile(const pcls_problem* p, int R, float* d_x, float lr, int n_st
   A.fixed = opt ? opt->d_fixed : nullptr;
   A.tol = opt ? opt->tol : 0.f;
   A.iters = opt ? opt->d_iters : nullptr;
-  void (*kern)(ProblemDev, TileArgs);
-  if (L.small) {
-    kern = L.acc64 ? tile_kernel<kMaxbShort, unsigned long long, true> : tile_kernel<kMaxbShort, unsigned int, true>;
-  } else if (L.acc64) {
-    kern = p->max_bucket <= kMaxbShort ? tile_kernel<kMaxbShort, unsigned long long, false>
-           : p->max_bucket <= kMaxbMid ? tile_kernel<kMaxbMid, unsigned long long, false>
-                                       : tile_kernel<kMaxbAll, unsigned long long, false>;
-  } else {
-    kern = p->max_bucket <= kMaxbShort ? tile_kernel<kMaxbShort, unsigned int, false>
-           : p->max_bucket <= kMaxbMid ? tile_kernel<kMaxbMid, unsigned int, false>
-                                       : tile_kernel<kMaxbAll, unsigned int, false>;
-  }
+  const TileKernel kern = tile_variant(p->max_bucket, L.acc64, L.logT, L.small);
   hipLaunchKernelGGL(kern, dim3(tiles), dim3(L.block), L.lds, stream, p->dev, A);
   PCLS_HIP(hipGetLastError(), "tile_kernel launch");
   return PCLS_OK;
