@@ -1797,7 +1797,15 @@ __global__ void __launch_bounds__(1024) batch_kernel(const BatchInst* __restrict
     A.fixed = nullptr;
     A.tol = 0.f;
     A.iters = nullptr;
-    resident_tile<MAXB, AT>(P, A, lds_raw);
+    // tiles of two, four and eight restarts have code of their own (see tile_kernel)
+    if (MAXB <= kMaxbShort && A.logT == 1)
+      resident_tile<MAXB, AT, MAXB <= kMaxbShort ? 1 : -1>(P, A, lds_raw);
+    else if (MAXB <= kMaxbShort && A.logT == 2)
+      resident_tile<MAXB, AT, MAXB <= kMaxbShort ? 2 : -1>(P, A, lds_raw);
+    else if (MAXB <= kMaxbShort && A.logT == 3)
+      resident_tile<MAXB, AT, MAXB <= kMaxbShort ? 3 : -1>(P, A, lds_raw);
+    else
+      resident_tile<MAXB, AT, -1>(P, A, lds_raw);
     __syncthreads();
   }
 }
