@@ -25,10 +25,16 @@ namespace pcls {
 //           FE = c0 + sum_{c < w} d_c Pr[C = c], from a truncated Poisson-binomial
 //           recursion and its adjoint (no complex nodes)
 //   CONST - sp constant: FE = c0, no literal work
-enum Kind : int32_t { KIND_PROD1 = 0, KIND_PROD2 = 1, KIND_DFT = 2, KIND_PMF = 3, KIND_CONST = 4 };
+//   THR   - a threshold (d constant on the window) of 9 to 64 literals whose bucket has
+//           enough empty slots to pad its window to exactly KMAX/2 counts: W - w pad
+//           slots hold literals whose event is certain, which shifts every count by
+//           W - w.  All classes of a bucket then run the same code, and the sums over
+//           the window are running sums.  (Listed as PMF up to 48 literals, as DFT above.)
+enum Kind : int32_t { KIND_PROD1 = 0, KIND_PROD2 = 1, KIND_DFT = 2, KIND_PMF = 3, KIND_CONST = 4, KIND_THR = 5 };
 constexpr int kNumKinds = 5;
 constexpr int kPmfWindow = 4;  // counts kept by the PMF kind, one lane per pair (k <= 8)
 constexpr int kPmfMaxK = 8;    // longest constraint of the one-lane PMF kind
+constexpr int kThrMaxK = 64;       // longest bucket of the THR kind
 constexpr int kPmfGroupMaxK = 48;  // longest constraint of the lane-group PMF kind (window <= bucket / 2)
 
 // Length buckets of the segment kernels: literals per constraint padded to KMAX,
@@ -52,22 +58,25 @@ constexpr int kMaxSegments = 4 * kNumBuckets;  // (kind, bucket) pairs of the no
 constexpr int kPadRows = 64;
 
 // Lanes per (constraint, restart) pair: one lane holds up to 16 literals of a
-// DFT or short product constraint or 8 of the PMF kind (register budget at 4 waves
-// per SIMD); longer constraints spread over G lanes (a power of two) of at most
-// 8 literals each (6 for the buckets 12, 24, ..., 192), the DFT kind of at most 16
-// (12).
+// DFT, THR or short product constraint or 8 of the PMF kind (register budget at 4
+// waves per SIMD); longer constraints spread over G lanes (a power of two) of at
+// most 8 literals each (6 for the buckets 12, 24, ..., 192), the DFT and THR kinds of
+// at most 16 (12).
 constexpr int lane_groups(int kmax, int per_lane = 8) {
   int g = 1;
   while (kmax > per_lane * g) g *= 2;
   return g;
 }
 constexpr int group_size(int kind, int kmax) {
-  if (kind == KIND_DFT) return lane_groups(kmax, 16);
+  if (kind == KIND_THR && kmax <= 16) return 2;
+  if (kind == KIND_DFT || kind == KIND_THR) return lane_groups(kmax, 16);
   return (kmax <= 8 || (kind != KIND_PMF && kmax <= 16)) ? 1 : lane_groups(kmax);
 }
 // What a constraint limits the tile width by (64 / width lanes are left for its
 // group): the lanes of at most 8 literals, also where a kind uses fewer.
-constexpr int tile_group(int kind, int kmax) { return kind == KIND_DFT ? lane_groups(kmax) : group_size(kind, kmax); }
+constexpr int tile_group(int kind, int kmax) {
+  return kind == KIND_DFT || kind == KIND_THR ? lane_groups(kmax) : group_size(kind, kmax);
+}
 
 // Bucket tables: which of the compiled lengths a plan uses.  Table 0 uses all of
 // them; table 1 only the exact ones up to 8 and the powers of two above (fewer
@@ -101,7 +110,8 @@ struct ClassRec {
   int32_t k;
   int32_t n_nodes;   // DFT, PMF: entries of the node table
   int32_t node_off;  // DFT, PMF: offset into the node table (entries)
-  int32_t window;    // PMF: window w
+  int32_t window;    // PMF, THR: window w
+  int32_t listed;    // kind it is counted under (pcls_info)
   int32_t sp_off;    // offset of sp[0..k] (int8) in the spectrum table
   float a, b;        // PROD1 node factor a + b y
   float c1, c2;      // PROD1 / PROD2 product weights
@@ -144,7 +154,8 @@ struct ProblemDev {
   int32_t n_codes;               // entries of litT
   const int32_t* c_par;          // per constraint of a product kind: two bf16 values, PROD1 b and c1,
                                  // PROD2 c2 and c1 (high and low half); of a DFT one: its class's
-                                 // node table entry; of a PMF one: its class
+                                 // node table entry; of a PMF one: its class; of a THR one: h and
+                                 // d_0 (two bf16 values)
   const float* c_w;              // per constraint weight
   const int32_t* row_ptr;        // planned-order CSR (extract / streaming engine)
   const int32_t* lit;            // planned-order literal codes

@@ -686,16 +686,17 @@ __device__ __forceinline__ void conv_trunc(const float (&u)[NU], const float (&v
 // constraints of 64 to 256 literals at 256 restarts 590 -> 388 us an evaluation;
 // the 77 constraints above 48 literals of the long-support instance (20000
 // variables, 4096 restarts) 0.32 -> 0.16 ms of a step.
+// coef: dF/dy_j = coef dFE/dpi_j, -h (1/2 where literals that are true count) times
+// the weight and the scale
 template <int N, class SK>
-__device__ __forceinline__ void dft_scatter(const float* gp, const int* code, float wg, int logT, int t, SK& sink) {
-  const float coef = -0.5f * wg;  // dFE/dy_j = -1/2 dFE/dpi_j
+__device__ __forceinline__ void count_scatter(const float* gp, const int* code, float coef, int logT, int t, SK& sink) {
 #pragma unroll
   for (int j = N - 1; j >= 0; --j) sink.add(lit_off(code[j], logT, t), flip(coef * gp[j], lit_sign(code[j])), code[j]);
 }
 // The literals of one half from the adjoint lam of its count distribution.
 template <int H, class SK>
-__device__ __forceinline__ void dft_half(const float* pi, float (&lam)[H + 1], const int* code, float wg, int logT,
-                                         int t, SK& sink) {
+__device__ __forceinline__ void count_half(const float* pi, float (&lam)[H + 1], const int* code, float coef, int logT,
+                                           int t, SK& sink) {
   float p[H], pre[H][H + 1], q[H + 1], gp[H];
 #pragma unroll
   for (int j = 0; j < H; ++j) {
@@ -706,8 +707,38 @@ __device__ __forceinline__ void dft_half(const float* pi, float (&lam)[H + 1], c
   }
   count_forward<H, H + 1>(p, pre, q);
   count_adjoint<H, H + 1>(p, pre, lam, gp);
-  dft_scatter<H>(gp, code, wg, logT, t, sink);
+  count_scatter<H>(gp, code, coef, logT, t, sink);
 }
+// The literals of both halves of a lane from the adjoint D of the lane's count
+// distribution qa * qb; returns sum_c (qa * qb)(c) D(c).
+template <int H, class SK>
+__device__ __forceinline__ float count_halves(const float* pi, const float (&qa)[H + 1], const float (&qb)[H + 1],
+                                              const float (&D)[2 * H + 1], const int* code, float coef, int logT, int t,
+                                              SK& sink) {
+  // per half: DA(a) = sum_b qb(b) D(a+b), DB(b) = sum_a qa(a) D(a+b)
+  __builtin_amdgcn_sched_barrier(0);
+  float DA[H + 1], DB[H + 1], fe = 0.f;
+#pragma unroll
+  for (int a = 0; a <= H; ++a) {
+    float sa = 0.f, sb = 0.f;
+#pragma unroll
+    for (int b = 0; b <= H; ++b) {
+      sa = fmaf(qb[b], D[a + b], sa);
+      sb = fmaf(qa[b], D[a + b], sb);
+    }
+    DA[a] = sa;
+    DB[a] = sb;
+    fe = fmaf(qa[a], sa, fe);
+  }
+  // one half after the other (the barriers keep the scheduler from running both at
+  // once, whose intermediate distributions do not fit the registers)
+  __builtin_amdgcn_sched_barrier(0);
+  count_half<H>(pi, DA, code, coef, logT, t, sink);
+  __builtin_amdgcn_sched_barrier(0);
+  count_half<H>(pi + H, DB, code + H, coef, logT, t, sink);
+  return fe;
+}
+
 template <int KMAX, int G, class SK>
 __device__ __forceinline__ void dft_pair(const ProblemDev& P, int z_off, const Fetched<KMAX / G>& fp, int lig, int t,
                                          int logT, const float* xs, SK& sink, float& fchunk, float gsc, float fsc) {
@@ -731,7 +762,7 @@ __device__ __forceinline__ void dft_pair(const ProblemDev& P, int z_off, const F
     }
     float gp[J];
     count_adjoint<J, J + 1>(pi, pre, lam, gp);
-    dft_scatter<J>(gp, fp.code, fp.w * gsc, logT, t, sink);
+    count_scatter<J>(gp, fp.code, -0.5f * (fp.w * gsc), logT, t, sink);
   } else {
     constexpr int H = J / 2;
     static_assert(J % 4 == 0 && J <= 16, "halves");
@@ -768,28 +799,70 @@ __device__ __forceinline__ void dft_pair(const ProblemDev& P, int z_off, const F
         z += 2 * J;
       }
     }
-    // per half: DA(a) = sum_b qb(b) D(a+b), DB(b) = sum_a qa(a) D(a+b)
-    __builtin_amdgcn_sched_barrier(0);
-    float DA[H + 1], DB[H + 1];
-#pragma unroll
-    for (int a = 0; a <= H; ++a) {
-      float sa = 0.f, sb = 0.f;
-#pragma unroll
-      for (int b = 0; b <= H; ++b) {
-        sa = fmaf(qb[b], D[a + b], sa);
-        sb = fmaf(qa[b], D[a + b], sb);
-      }
-      DA[a] = sa;
-      DB[a] = sb;
-      fe = fmaf(qa[a], sa, fe);
-    }
-    // one half after the other (the barriers keep the scheduler from running
-    // both at once, whose intermediate distributions do not fit the registers)
-    __builtin_amdgcn_sched_barrier(0);
-    dft_half<H>(pi, DA, fp.code, fp.w * gsc, logT, t, sink);
-    __builtin_amdgcn_sched_barrier(0);
-    dft_half<H>(pi + H, DB, fp.code + H, fp.w * gsc, logT, t, sink);
+    fe = count_halves<H>(pi, qa, qb, D, fp.code, -0.5f * (fp.w * gsc), logT, t, sink);
   }
+  if (lig == 0) fchunk = fmaf(fp.w * fsc, fe, fchunk);
+}
+
+// THR kind: a threshold, FE = c0 + d_0 Pr[C < W] with W = KMAX/2 in every class of the
+// bucket (certain pad slots shift the counts).  Lane distributions q as in the DFT
+// kind; the rest of the group enters through D(c) = d_0 Pr[others < W - c]:
+// two lanes, running sums of the other's q; four, with x1
+// the partner's q and z the other pair's convolved total (truncated to W counts),
+// D(c) = sum_a x1(a) d_0 S(W - c - a), S the running sums of z.  Every step adds
+// products of probabilities.  Bound by VALU issue: about 34, 50, 73 and 89
+// operations a slot at 9..16, 17..32, 33..48 and 49..64 literals.  Windows at a
+// class's own offset took W^2/2 products or a barrel shift to read, scalar loads per
+// class, turns by class, and lane groups of 8 literals to fit them: 51, 88 and 212
+// operations a literal up to 48, and the DFT kind above.
+template <int KMAX, int G, class SK>
+__device__ __forceinline__ void thr_pair(const Fetched<KMAX / G>& fp, int lig, int t, int logT, const float* xs, SK& sink,
+                                         float& fchunk, float gsc, float fsc) {
+  constexpr int J = KMAX / G, H = J / 2, W = KMAX / 2;
+  static_assert(J % 2 == 0 && J <= 16 && (G == 2 || G == 4), "shape");
+  const int T = 1 << logT;
+  const float h = __uint_as_float((unsigned)fp.cls & 0xffff0000u), d0 = __uint_as_float((unsigned)fp.cls << 16);
+  float pi[J];
+#pragma unroll
+  for (int j = 0; j < J; ++j)
+    pi[j] = fmaf(-h, flip(x_at(xs, lit_off(fp.code[j], logT, t)), lit_sign(fp.code[j])), 0.5f);
+  float qa[H + 1], qb[H + 1], D[J + 1];
+  count_only<H, H + 1>(pi, qa);
+  count_only<H, H + 1>(pi + H, qb);
+  float q[J + 1], x1[J + 1];
+  conv_trunc(qa, qb, q);
+  xor_exchange(q, x1, T);
+  if constexpr (G == 2) {
+    float run = 0.f;
+#pragma unroll
+    for (int c = J; c >= 0; --c) {  // D(c) = d_0 sum of x1 below W - c = J - c
+      D[c] = d0 * run;
+      run += x1[J - c];
+    }
+  } else {
+    float z[W];
+    {
+      float y2[W];
+      conv_trunc(q, x1, y2);
+      xor_exchange(y2, z, 2 * T);
+    }
+    float dz[W];  // d_0 times the sum of z below W - i
+    float run = 0.f;
+#pragma unroll
+    for (int i = W - 1; i >= 0; --i) {
+      run += z[W - 1 - i];
+      dz[i] = d0 * run;
+    }
+#pragma unroll
+    for (int c = 0; c <= J; ++c) {
+      float acc = 0.f;
+#pragma unroll
+      for (int a = 0; a <= J; ++a)
+        if (c + a < W) acc = fmaf(x1[a], dz[c + a], acc);
+      D[c] = acc;
+    }
+  }
+  const float fe = count_halves<H>(pi, qa, qb, D, fp.code, -h * (fp.w * gsc), logT, t, sink);
   if (lig == 0) fchunk = fmaf(fp.w * fsc, fe, fchunk);
 }
 
@@ -1065,7 +1138,7 @@ __device__ __forceinline__ void prod_pair_r2(const Fetched<KMAX>& fp, int t2, in
 // pair per lane: their register budget goes to the long groups.
 template <int KIND, int J, int MAXB>
 constexpr int pairs_per_lane() {
-  return (KIND == KIND_DFT || KIND == KIND_PMF || MAXB > kMaxbShort) ? 1 : (J <= 4 ? 4 : (J <= 8 ? 2 : 1));
+  return (KIND == KIND_DFT || KIND == KIND_PMF || KIND == KIND_THR || MAXB > kMaxbShort) ? 1 : (J <= 4 ? 4 : (J <= 8 ? 2 : 1));
 }
 
 template <int J, int U>
@@ -1231,6 +1304,8 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
       auto eval_pair = [&](auto& sink, const Fetched<J>& f) {
         if constexpr (KIND == KIND_DFT) {
           dft_pair<KMAX, G>(P, S.z_off, f, lig, t, logT, xs, sink, fchunk, gsc, fsc);
+        } else if constexpr (KIND == KIND_THR) {
+          thr_pair<KMAX, G>(f, lig, t, logT, xs, sink, fchunk, gsc, fsc);
         } else if constexpr (KIND == KIND_PMF && KMAX > 8) {
           // lanes take turns by class (the first remaining lane's class each
           // round; one round for a class-uniform chunk), so the class record and
@@ -1285,7 +1360,7 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
     }
     facc.own += fixed_term(fchunk);
   };
-  constexpr bool kHeavy = KIND == KIND_DFT || (KIND == KIND_PMF && KMAX > 8);
+  constexpr bool kHeavy = KIND == KIND_DFT || (KIND == KIND_THR && KMAX > 16) || (KIND == KIND_PMF && KMAX > 8);
   if constexpr (CL)
     deal_chunks<FetchedU<J, U>>(S.c_count, per_wave, L, fetch, eval);
   else
@@ -1330,6 +1405,14 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
   X(KIND, 11, 32)                        \
   X(KIND, 12, 48)
 
+#define PCLS_THR_BUCKET_CASES(KIND, X) \
+  X(KIND, 8, 12)                        \
+  X(KIND, 9, 16)                        \
+  X(KIND, 10, 24)                       \
+  X(KIND, 11, 32)                       \
+  X(KIND, 12, 48)                       \
+  X(KIND, 13, 64)
+
 #define PCLS_CASE(KIND, B, KMAX)                                                                    \
   case (KIND)*kNumBuckets + (B):                                                                    \
     if constexpr ((B) <= MAXB) run_segment<KIND, KMAX, MAXB, AT, ST, CL>(P, S, xs, gs, facc, gsc, fsc, tid, logT, ctr, L, so); \
@@ -1344,6 +1427,7 @@ __device__ __forceinline__ void run_any_segment(const ProblemDev& P, const Segme
     PCLS_BUCKET_CASES(KIND_PROD2, PCLS_CASE)
     PCLS_BUCKET_CASES(KIND_DFT, PCLS_CASE)
     PCLS_PMF_BUCKET_CASES(KIND_PMF, PCLS_CASE)
+    PCLS_THR_BUCKET_CASES(KIND_THR, PCLS_CASE)
     default:
       break;
   }
@@ -2644,7 +2728,7 @@ int32_t pcls_problem_info(const pcls_problem* p, pcls_info* info) {
   info->block_threads = p->block_threads;
   info->workspace_bytes = p->image.size();
   info->lds_bytes_per_restart = (size_t)state_rows(p) * 2 * sizeof(float);
-  for (int32_t c : p->c_cls) ++info->cons_by_kind[p->classes[(size_t)c].kind];
+  for (int32_t c : p->c_cls) ++info->cons_by_kind[p->classes[(size_t)c].listed];
   info->bucket_table = p->bucket_table;
   clear_error();
   return PCLS_OK;

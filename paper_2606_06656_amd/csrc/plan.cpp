@@ -232,6 +232,21 @@ static void classify(const std::vector<int>& sp, bool force_generic, int table, 
   C.kind = KIND_DFT;
 }
 
+// Thresholds of long buckets (KIND_THR): d constant on the shorter window, of w
+// counts, and room for W - w certain pad slots.  Sets the window, h and d_0.
+static bool aligned_threshold(const std::vector<int>& sp, int table, ClassRec& C, float* h, float* d0) {
+  const int k = (int)sp.size() - 1, kb = kBucketKmax[bucket_of(k, table)];
+  if (k <= kPmfMaxK || kb > kThrMaxK || (C.kind != KIND_PMF && C.kind != KIND_DFT)) return false;
+  std::vector<float> d((size_t)k + 1);
+  const int w = pmf_window(sp, d.data(), h, k + 1);
+  if (2 * w > kb || kb / 2 - w > kb - k) return false;
+  for (int c = 1; c < w; ++c)
+    if (d[(size_t)c] != d[0]) return false;
+  C.window = w;
+  *d0 = d[0];
+  return true;
+}
+
 // PMF kind: the shorter of the two windows.  Counting true literals,
 // FE = sp_k + sum_{t < w} (sp_t - sp_k) Pr[T = t] with w = 1 + the last t where
 // sp_t != sp_k; counting false ones (F = k - T), FE = sp_0 + sum_{f < w}
@@ -327,15 +342,15 @@ static int32_t dft_powers(int kmax, const Roots& w, std::vector<NodeRec>& nodes)
 
 // Parameters of a product class in one word: two bf16 values, all of them exact
 // (0, +-1/2, +-1, +-2).
-static int32_t product_params(const ClassRec& C) {
+static int32_t bf16_pair(float hi, float lo) {
   auto top = [](float v) {
     uint32_t u;
     std::memcpy(&u, &v, sizeof u);
     return u & 0xffff0000u;
   };
-  const float hi = C.kind == KIND_PROD1 ? C.b : C.c2;
-  return (int32_t)(top(hi) | (top(C.c1) >> 16));
+  return (int32_t)(top(hi) | (top(lo) >> 16));
 }
+static int32_t product_params(const ClassRec& C) { return bf16_pair(C.kind == KIND_PROD1 ? C.b : C.c2, C.c1); }
 
 // Violated counts of a spectrum, packed (ClassRec::violated).
 static uint32_t violated_counts(const std::vector<int>& sp) {
@@ -431,6 +446,14 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
       C.k = k;
       classify(sp, force_generic, P->bucket_table, C);
       C.violated = violated_counts(sp);
+      C.listed = C.kind;
+      float h = 0.f, d0 = 0.f;
+      if (!force_generic && aligned_threshold(sp, P->bucket_table, C, &h, &d0)) {
+        C.kind = KIND_THR;
+        C.a = h;
+        C.c1 = d0;
+        C.c0 = (float)(h > 0.f ? sp[(size_t)k] : sp[0]);
+      }
       if (C.kind == KIND_DFT) {
         const int kmax = kBucketKmax[bucket_of(k, P->bucket_table)];
         dft_class(sp, kmax, roots(kmax), C, P->nodes);
@@ -521,8 +544,8 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
   for (int c = 0; c < m; ++c) order[c] = c;
   auto seg_key = [&](int c) {
     const ClassRec& C = P->classes[cls_orig[c]];
-    int kind = C.kind;
-    int b = kind == KIND_CONST ? 0 : bucket_of(C.k, P->bucket_table);
+    int kind = C.kind == KIND_CONST ? 99 : C.kind;
+    int b = C.kind == KIND_CONST ? 0 : bucket_of(C.k, P->bucket_table);
     return std::make_tuple(kind, b, cls_orig[c], c);
   };
   std::sort(order.begin(), order.end(), [&](int a, int b) { return seg_key(a) < seg_key(b); });
@@ -594,6 +617,7 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
         if (P->c_par[e] != S.par_fixed) S.par_fixed = 0;
       }
       if (C.kind == KIND_DFT) P->c_par[e] = C.node_off;
+      if (C.kind == KIND_THR) P->c_par[e] = bf16_pair(C.a, C.c1);
       if (C.kind == KIND_PMF) {
         S.m_max = std::max(S.m_max, C.window);
         P->c_par[e] = P->c_cls[e];
@@ -617,9 +641,14 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
       // (1 - y)/2 and for counts of false literals (h < 0), y = +1 otherwise
       const ClassRec& C = P->classes[P->c_cls[cj]];
       const bool neg = (C.kind == KIND_PROD1 && C.b < 0.f) || (C.kind == KIND_PMF && (C.k > kPmfMaxK && pmf_counts_false_of(P->nodes, C)));
-      for (int i = P->c_k[cj]; i < kmax; ++i)
+      // THR: the first W - w pad slots hold certain events, pi = 1/2 - h y = 1, the
+      // others impossible ones, pi = 0
+      const int certain = C.kind == KIND_THR ? kmax / 2 - C.window : 0;
+      for (int i = P->c_k[cj]; i < kmax; ++i) {
+        const bool flip = C.kind == KIND_THR ? (i - P->c_k[cj] < certain) == (C.a > 0.f) : neg;
         P->litT[(size_t)S.lit_base + (size_t)i * S.c_count + q] =
-            (int32_t)((uint32_t)(n + (q + i) % kPadRows) | (neg ? 0x80000000u : 0u));
+            (int32_t)((uint32_t)(n + (q + i) % kPadRows) | (flip ? 0x80000000u : 0u));
+      }
     }
     const int G = group_size(S.kind, kmax);
     if (kmax > 8 && kmax <= 64) balance_long_slots(P->litT.data() + S.lit_base, S.c_count, kmax, G);
@@ -637,6 +666,7 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
     auto cost = [](const Segment& s) {
       const int k = kBucketKmax[s.bucket];
       return s.kind == KIND_DFT ? (group_size(KIND_DFT, k) == 1 ? 6 * k : k * (k / 2 + 8))
+             : s.kind == KIND_THR ? k * (3 + k / 10)
              : s.kind == KIND_PMF ? (k <= kPmfMaxK ? 6 * k : k * (k / 2 + 2))
              : (s.kind == KIND_PROD2 ? 2 * k : k);
     };
