@@ -20,10 +20,11 @@ namespace pcls {
 //           a lane group at the K = KMAX+1 complex roots of unity of the length bucket
 //   PMF   - sp constant outside a window of w counts at one end (thresholds,
 //           at-most-one, exactly-kappa near an end), w <= 4 for k <= 8 (one lane
-//           per pair) and w <= KMAX/2 of the length bucket for 8 < k <= 48 (lane
+//           per pair) and w <= KMAX/2 of the length bucket for 17 to 48 literals (lane
 //           groups): with C the number of true literals (or of false ones),
 //           FE = c0 + sum_{c < w} d_c Pr[C = c], from a truncated Poisson-binomial
-//           recursion and its adjoint (no complex nodes)
+//           recursion and its adjoint (no complex nodes).  (Windows of 9 to 16 literals
+//           are listed as PMF too and run as DFT, on one lane without nodes.)
 //   CONST - sp constant: FE = c0, no literal work
 //   THR   - a threshold (d constant on the window) of 9 to 64 literals whose bucket has
 //           enough empty slots to pad its window to exactly KMAX/2 counts: W - w pad
@@ -57,25 +58,24 @@ constexpr int kMaxSegments = 4 * kNumBuckets;  // (kind, bucket) pairs of the no
 // the constraint's slots.
 constexpr int kPadRows = 64;
 
-// Lanes per (constraint, restart) pair: one lane holds up to 16 literals of a
-// DFT, THR or short product constraint or 8 of the PMF kind (register budget at 4
-// waves per SIMD); longer constraints spread over G lanes (a power of two) of at
-// most 8 literals each (6 for the buckets 12, 24, ..., 192), the DFT and THR kinds of
-// at most 16 (12).
+// Lanes per (constraint, restart) pair: one lane holds up to 16 literals (register
+// budget at 4 waves per SIMD); longer constraints spread over G lanes (a power of
+// two) of at most 16 (12 for the buckets 24, 48, ...), products above 16 literals and
+// the windows of 9 to 16 of at most 8 (6).
 constexpr int lane_groups(int kmax, int per_lane = 8) {
   int g = 1;
   while (kmax > per_lane * g) g *= 2;
   return g;
 }
 constexpr int group_size(int kind, int kmax) {
-  if (kind == KIND_THR && kmax <= 16) return 2;
-  if (kind == KIND_DFT || kind == KIND_THR) return lane_groups(kmax, 16);
-  return (kmax <= 8 || (kind != KIND_PMF && kmax <= 16)) ? 1 : lane_groups(kmax);
+  if (kmax <= 8) return 1;
+  if (kind == KIND_THR || kind == KIND_PMF) return kmax <= 16 ? 2 : lane_groups(kmax, 16);
+  return kind == KIND_DFT ? lane_groups(kmax, 16) : (kmax <= 16 ? 1 : lane_groups(kmax));
 }
 // What a constraint limits the tile width by (64 / width lanes are left for its
 // group): the lanes of at most 8 literals, also where a kind uses fewer.
 constexpr int tile_group(int kind, int kmax) {
-  return kind == KIND_DFT || kind == KIND_THR ? lane_groups(kmax) : group_size(kind, kmax);
+  return kind == KIND_PROD1 || kind == KIND_PROD2 ? group_size(kind, kmax) : lane_groups(kmax);
 }
 
 // Bucket tables: which of the compiled lengths a plan uses.  Table 0 uses all of
@@ -130,8 +130,8 @@ struct ClassRec {
 //   DFT on one lane: a class has sp_t - sp_k for t = 0..KMAX (0 past k).
 //   PMF of k <= 8 literals: one entry {d_0, d_1, d_2, d_3, h, 0, 0, 0}, where the
 //     counted event of literal i has probability 1/2 - h y_i (h = 1/2: true, -1/2:
-//     false); a longer one has five: d_0..d_31 (zero past its window), h, a
-//     threshold flag (d constant on the window), then padding.
+//     false); a longer one has five: d_0..d_31 (zero past its window), h, then
+//     padding.
 struct NodeRec {
   float f[8];
 };

@@ -47,6 +47,17 @@ __device__ __forceinline__ cf cmul(cf a, cf b) {
   return {fmaf(a.r, b.r, -a.i * b.i), fmaf(a.r, b.i, a.i * b.r)};
 }
 
+// The lane index, formed where it is used (volatile: not hoisted or shared).  Lane
+// arithmetic hoisted out of the step loop for every segment's code at once exhausts
+// the register budget, and a thread index kept over them was itself reloaded from
+// scratch memory at the start of every segment (a memory latency, some 45 times a
+// step on the long-support instance).
+__device__ __forceinline__ int lane_id() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
+
 template <int G>
 struct Log2 {
   static constexpr int v = 1 + Log2<G / 2>::v;
@@ -505,137 +516,6 @@ __device__ __forceinline__ void count_adjoint(const float* pi, const float (&pre
   }
 }
 
-// PMF kind for constraints of 9 to 32 literals whose spectrum is constant past
-// a window of at most KMAX/2 counts at one end (thresholds near the middle such
-// as at-least-ceil(k/2), exactly-one, at-most-one, exactly-kappa near an end).
-// The pair's G lanes hold J literals each, in two halves of J/2.  Each half
-// runs the truncated count recursion of the PMF kind, giving its count
-// distribution qa, qb; the lane's own count has q = qa * qb (convolution).  The
-// count over the other lanes of the group has the distribution E, the
-// truncated convolution of their q (G = 2: the partner's q; G = 4: the
-// partner's q convolved with the other pair's convolved total), obtained by
-// lane exchanges.  With D(c) = sum_b d_{c+b} E(b) (d zero past the window),
-// FE = c0 + sum_c q(c) D(c) in every lane of the group; as a function of half
-// a's distribution, FE = c0 + sum_a qa(a) DA(a) with DA(a) = sum_b qb(b) D(a+b),
-// so each literal's gradient is the adjoint of its half's recursion started
-// from DA (or DB).  Every step adds products of probabilities: no
-// cancellation, and about (J + W) operations per literal against about 14 per
-// node and literal (k/2 nodes) on the DFT path.
-// Class data (node table entries read as floats): d_0..d_31 (zero past the
-// window), h at 32, and at 33 a flag for threshold windows (d constant on the
-// window [0, w), w the class's window).
-template <int KMAX, int G, class SK>
-__device__ __forceinline__ void pmfg_pair(const ProblemDev& P, int cls, const Fetched<KMAX / G>& fp, int lig, int t,
-                                          int logT, const float* xs, SK& sink, float& fchunk, float gsc, float fsc) {
-  constexpr int J = KMAX / G;
-  constexpr int H = J / 2;                    // literals per half
-  constexpr int MH = H + 1;                   // counts of a half (never truncated: H + 1 <= W)
-  constexpr int W = KMAX / 2;                 // widest window of the bucket
-  constexpr int WL = J + 1 < W ? J + 1 : W;   // counts of one lane kept
-  static_assert(G == 2 || G == 4, "lane groups of 2 or 4 (8: pmfg8_pair)");
-  static_assert(J % 2 == 0 && MH <= W, "halves");
-  const int T = 1 << logT;
-  kptr<ClassRec> classes = kconst(P.classes);
-  kptr<float> dt = reinterpret_cast<kptr<float>>(kconst(P.nodes) + classes[cls].node_off);
-  float d[W];
-#pragma unroll
-  for (int c = 0; c < W; ++c) d[c] = dt[c];
-  const float h = dt[32];
-
-  float pi[J];
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const int code = fp.code[j];  // a pad slot reads y = 2h: pi = 0, it adds nothing to the count
-    pi[j] = fmaf(-h, flip(x_at(xs, lit_off(code, logT, t)), lit_sign(code)), 0.5f);
-  }
-  float prea[H][MH], preb[H][MH], qa[MH], qb[MH];
-  count_forward<H, MH>(pi, prea, qa);
-  count_forward<H, MH>(pi + H, preb, qb);
-  float q[WL];
-#pragma unroll
-  for (int c = 0; c < WL; ++c) {
-    float acc = 0.f;
-#pragma unroll
-    for (int a = 0; a < MH; ++a)
-      if (c - a >= 0 && c - a < MH) acc = fmaf(qa[a], qb[c - a], acc);
-    q[c] = acc;
-  }
-
-  // D(c) = sum_b d_{c+b} E(b)
-  float D[WL];
-  if constexpr (G == 2) {
-    float e[WL];
-    xor_exchange(q, e, T);
-#pragma unroll
-    for (int c = 0; c < WL; ++c) {
-      float acc = 0.f;
-#pragma unroll
-      for (int b = 0; b < WL; ++b)
-        if (c + b < W) acc = fmaf(d[c + b], e[b], acc);
-      D[c] = acc;
-    }
-  } else {
-    float x1[WL];
-    xor_exchange(q, x1, T);  // partner in the same half of the group
-    float y2[W];             // that half's total count, truncated
-#pragma unroll
-    for (int c = 0; c < W; ++c) {
-      float acc = 0.f;
-#pragma unroll
-      for (int a = 0; a < WL; ++a)
-        if (c - a >= 0 && c - a < WL) acc = fmaf(q[a], x1[c - a], acc);
-      y2[c] = acc;
-    }
-    float z[W];
-    xor_exchange(y2, z, 2 * T);  // the other half's total
-    // dz(j) = sum_b d_{j+b} z(b); D(c) = sum_a x1(a) dz(c + a)
-    float dz[W];
-#pragma unroll
-    for (int j = 0; j < W; ++j) {
-      float acc = 0.f;
-#pragma unroll
-      for (int b = 0; b < W; ++b)
-        if (j + b < W) acc = fmaf(d[j + b], z[b], acc);
-      dz[j] = acc;
-    }
-#pragma unroll
-    for (int c = 0; c < WL; ++c) {
-      float acc = 0.f;
-#pragma unroll
-      for (int a = 0; a < WL; ++a)
-        if (c + a < W) acc = fmaf(x1[a], dz[c + a], acc);
-      D[c] = acc;
-    }
-  }
-  // per half: DA(a) = sum_b qb(b) D(a+b), DB(b) = sum_a qa(a) D(a+b)
-  float DA[MH], DB[MH];
-#pragma unroll
-  for (int a = 0; a < MH; ++a) {
-    float sa = 0.f, sb = 0.f;
-#pragma unroll
-    for (int b = 0; b < MH; ++b)
-      if (a + b < WL) {
-        sa = fmaf(qb[b], D[a + b], sa);
-        sb = fmaf(qa[b], D[a + b], sb);
-      }
-    DA[a] = sa;
-    DB[a] = sb;
-  }
-  float fe = 0.f;
-#pragma unroll
-  for (int a = 0; a < MH; ++a) fe = fmaf(qa[a], DA[a], fe);
-  if (lig == 0) fchunk = fmaf(fp.w * fsc, fe, fchunk);
-
-  // dFE/dy_j = -h dFE/dpi_j
-  float gp[J];
-  count_adjoint<H, MH>(pi, prea, DA, gp);
-  count_adjoint<H, MH>(pi + H, preb, DB, gp + H);
-  const float coef = -h * (fp.w * gsc);
-#pragma unroll
-  for (int j = J - 1; j >= 0; --j)
-    sink.add(lit_off(fp.code[j], logT, t), flip(coef * gp[j], lit_sign(fp.code[j])), fp.code[j]);
-}
-
 // Count distribution of N literals (probabilities pi), truncated to M counts,
 // without keeping the intermediate distributions.
 template <int N, int M>
@@ -815,13 +695,28 @@ __device__ __forceinline__ void dft_pair(const ProblemDev& P, int z_off, const F
 // class's own offset took W^2/2 products or a barrel shift to read, scalar loads per
 // class, turns by class, and lane groups of 8 literals to fit them: 51, 88 and 212
 // operations a literal up to 48, and the DFT kind above.
-template <int KMAX, int G, class SK>
-__device__ __forceinline__ void thr_pair(const Fetched<KMAX / G>& fp, int lig, int t, int logT, const float* xs, SK& sink,
-                                         float& fchunk, float gsc, float fsc) {
+//
+// PMF kind above 16 literals (!THR): windows of at most W counts that are not a
+// threshold or have no room to be aligned (at-most-one, exactly-one, exactly-kappa).
+// The same with the class's own d, which the caller makes wave-uniform (cls; node
+// table entries read as floats: d_0..d_31, zero past the window, h at 32):
+// D(c) = sum_b d_{c+b} x1(b) for two lanes, dz(j) = sum_b d_{j+b} z(b) for four,
+// W^2/2 products more.
+template <int KMAX, int G, bool THR, class SK>
+__device__ __forceinline__ void window_pair(const ProblemDev& P, int cls, const Fetched<KMAX / G>& fp, int lig, int t,
+                                            int logT, const float* xs, SK& sink, float& fchunk, float gsc, float fsc) {
   constexpr int J = KMAX / G, H = J / 2, W = KMAX / 2;
   static_assert(J % 2 == 0 && J <= 16 && (G == 2 || G == 4), "shape");
   const int T = 1 << logT;
-  const float h = __uint_as_float((unsigned)fp.cls & 0xffff0000u), d0 = __uint_as_float((unsigned)fp.cls << 16);
+  kptr<float> d = nullptr;
+  float h, d0 = 0.f;
+  if constexpr (THR) {
+    h = __uint_as_float((unsigned)fp.cls & 0xffff0000u);
+    d0 = __uint_as_float((unsigned)fp.cls << 16);
+  } else {
+    d = reinterpret_cast<kptr<float>>(kconst(P.nodes) + kconst(P.classes)[cls].node_off);
+    h = d[32];
+  }
   float pi[J];
 #pragma unroll
   for (int j = 0; j < J; ++j)
@@ -832,12 +727,20 @@ __device__ __forceinline__ void thr_pair(const Fetched<KMAX / G>& fp, int lig, i
   float q[J + 1], x1[J + 1];
   conv_trunc(qa, qb, q);
   xor_exchange(q, x1, T);
-  if constexpr (G == 2) {
+  if constexpr (G == 2 && THR) {
     float run = 0.f;
 #pragma unroll
     for (int c = J; c >= 0; --c) {  // D(c) = d_0 sum of x1 below W - c = J - c
       D[c] = d0 * run;
       run += x1[J - c];
+    }
+  } else if constexpr (G == 2) {
+#pragma unroll
+    for (int c = 0; c <= J; ++c) {
+      float acc = 0.f;
+#pragma unroll
+      for (int b = 0; c + b < W; ++b) acc = fmaf(d[c + b], x1[b], acc);
+      D[c] = acc;
     }
   } else {
     float z[W];
@@ -846,12 +749,22 @@ __device__ __forceinline__ void thr_pair(const Fetched<KMAX / G>& fp, int lig, i
       conv_trunc(q, x1, y2);
       xor_exchange(y2, z, 2 * T);
     }
-    float dz[W];  // d_0 times the sum of z below W - i
-    float run = 0.f;
+    float dz[W];
+    if constexpr (THR) {  // d_0 times the sum of z below W - i
+      float run = 0.f;
 #pragma unroll
-    for (int i = W - 1; i >= 0; --i) {
-      run += z[W - 1 - i];
-      dz[i] = d0 * run;
+      for (int i = W - 1; i >= 0; --i) {
+        run += z[W - 1 - i];
+        dz[i] = d0 * run;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < W; ++i) {
+        float acc = 0.f;
+#pragma unroll
+        for (int b = 0; i + b < W; ++b) acc = fmaf(d[i + b], z[b], acc);
+        dz[i] = acc;
+      }
     }
 #pragma unroll
     for (int c = 0; c <= J; ++c) {
@@ -864,159 +777,6 @@ __device__ __forceinline__ void thr_pair(const Fetched<KMAX / G>& fp, int lig, i
   }
   const float fe = count_halves<H>(pi, qa, qb, D, fp.code, -h * (fp.w * gsc), logT, t, sink);
   if (lig == 0) fchunk = fmaf(fp.w * fsc, fe, fchunk);
-}
-
-// The lane at xor distance 4 T in the lane's group of eight.  With T = 1 the
-// group is an 8-lane half-row: the lower quad reads 4 lanes up, the upper quad 4
-// lanes down (two DPP row shifts and a select); otherwise a wave shuffle.  The
-// partner is the same lane either way, so results do not depend on T (the four
-// lanes of a quad hold totals summed in different orders, which may differ in
-// the last bit).
-template <int N>
-__device__ __forceinline__ void other_quad(const float (&src)[N], float (&dst)[N], int T, int lig) {
-  if (T == 1) {
-    const bool upper = (lig & 4) != 0;
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const float up = row_shl<4>(src[i]), dn = row_shr<4>(src[i]);
-      dst[i] = upper ? dn : up;
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < N; ++i) dst[i] = __shfl_xor(src[i], 4 * T);
-  }
-}
-
-// PMF kind for 33 to 48 literals (lane groups of G = 8, J = KMAX/8 literals per
-// lane, window up to W = KMAX/2 counts): as pmfg_pair with one more level of the
-// butterfly, the other quad's total z4.  E = x1 * z2 * z4 is not formed; with
-// R4(j) = sum_b d_{j+b} z4(b) and R2(j) = sum_a z2(a) R4(j+a),
-// D(c) = sum_a x1(a) R2(c+a).  For a threshold window (d = d_0 on [0, w)),
-// R4(j) = d_0 S(w - j), S(m) the sum of z4 below m, read at the wave-uniform
-// offset W - w by a barrel shift of uniform branches instead of the W^2/2
-// products of the general correlation.  To stay within the register budget the
-// lane's local distributions are computed twice: once without their
-// intermediate distributions for the butterfly, then with them for the adjoint.
-template <int KMAX, class SK>
-__device__ __forceinline__ void pmfg8_pair(const ProblemDev& P, int cls, const Fetched<KMAX / 8>& fp, int lig,
-                                           int t, int logT, const float* xs, SK& sink, float& fchunk, float gsc,
-                                           float fsc) {
-  constexpr int J = KMAX / 8;
-  constexpr int H = J / 2;
-  constexpr int MH = H + 1;
-  constexpr int W = KMAX / 2;
-  constexpr int WL = J + 1;            // counts of one lane (J + 1 <= W)
-  constexpr int W2 = 2 * WL - 1;       // counts of a pair (2 J + 1 <= W)
-  static_assert(J % 2 == 0 && W2 <= W, "shape");
-  const int T = 1 << logT;
-  kptr<ClassRec> classes = kconst(P.classes);
-  kptr<float> dt = reinterpret_cast<kptr<float>>(kconst(P.nodes) + classes[cls].node_off);
-  const int w = classes[cls].window;
-  const float h = dt[32];
-  const bool thr = dt[33] != 0.f;
-
-  float pi[J];
-#pragma unroll
-  for (int j = 0; j < J; ++j)
-    pi[j] = fmaf(-h, flip(x_at(xs, lit_off(fp.code[j], logT, t)), lit_sign(fp.code[j])), 0.5f);
-
-  // butterfly over the group: D(c) for the lane's local count c < WL
-  float D[WL];
-  {
-    float x1[WL];
-    {
-      float qa[MH], qb[MH], q[WL];
-      count_only<H, MH>(pi, qa);
-      count_only<H, MH>(pi + H, qb);
-      conv_trunc(qa, qb, q);
-      xor_exchange(q, x1, T);
-      float y2[W2];
-      conv_trunc(q, x1, y2);
-      float z2[W2];
-      xor_exchange(y2, z2, 2 * T);
-      float R4[W];
-      {
-        float y4[W];
-        conv_trunc(y2, z2, y4);
-        float z4[W];
-        other_quad(y4, z4, T, lig);
-        if (thr) {
-          // A(i) = sum_{b < W - i} z4(b), then shifted left by W - w: A(j) -> S(w - j)
-          float A[W];
-          float run = 0.f;
-#pragma unroll
-          for (int i = W - 1; i >= 0; --i) {
-            run += z4[W - 1 - i];
-            A[i] = run;
-          }
-          const int sft = W - w;  // wave-uniform, 0 <= sft < W
-#pragma unroll
-          for (int k = 1; k < W; k <<= 1) {
-            if (sft & k) {
-#pragma unroll
-              for (int i = 0; i < W; ++i) A[i] = i + k < W ? A[i + k] : 0.f;
-            }
-          }
-          const float d0 = dt[0];
-#pragma unroll
-          for (int j = 0; j < W; ++j) R4[j] = d0 * A[j];
-        } else {
-#pragma unroll
-          for (int j = 0; j < W; ++j) {
-            float acc = 0.f;
-#pragma unroll
-            for (int b = 0; b < W; ++b)
-              if (j + b < W) acc = fmaf(dt[j + b], z4[b], acc);
-            R4[j] = acc;
-          }
-        }
-      }
-      float R2[W2];
-#pragma unroll
-      for (int j = 0; j < W2; ++j) {
-        float acc = 0.f;
-#pragma unroll
-        for (int a = 0; a < W2; ++a)
-          if (j + a < W) acc = fmaf(z2[a], R4[j + a], acc);
-        R2[j] = acc;
-      }
-#pragma unroll
-      for (int c = 0; c < WL; ++c) {
-        float acc = 0.f;
-#pragma unroll
-        for (int a = 0; a < WL; ++a) acc = fmaf(x1[a], R2[c + a], acc);
-        D[c] = acc;
-      }
-    }
-  }
-
-  // the lane's halves again, with their intermediate distributions
-  float prea[H][MH], preb[H][MH], qa[MH], qb[MH];
-  count_forward<H, MH>(pi, prea, qa);
-  count_forward<H, MH>(pi + H, preb, qb);
-  float DA[MH], DB[MH];
-#pragma unroll
-  for (int a = 0; a < MH; ++a) {
-    float sa = 0.f, sb = 0.f;
-#pragma unroll
-    for (int b = 0; b < MH; ++b) {
-      sa = fmaf(qb[b], D[a + b], sa);
-      sb = fmaf(qa[b], D[a + b], sb);
-    }
-    DA[a] = sa;
-    DB[a] = sb;
-  }
-  float fe = 0.f;
-#pragma unroll
-  for (int a = 0; a < MH; ++a) fe = fmaf(qa[a], DA[a], fe);
-  if (lig == 0) fchunk = fmaf(fp.w * fsc, fe, fchunk);
-  float gp[J];
-  count_adjoint<H, MH>(pi, prea, DA, gp);
-  count_adjoint<H, MH>(pi + H, preb, DB, gp + H);
-  const float coef = -h * (fp.w * gsc);
-#pragma unroll
-  for (int j = J - 1; j >= 0; --j)
-    sink.add(lit_off(fp.code[j], logT, t), flip(coef * gp[j], lit_sign(fp.code[j])), fp.code[j]);
 }
 
 // Per-lane objective partial sums (exact integers): `own` for restart
@@ -1204,11 +964,10 @@ __device__ __forceinline__ void deal_chunks(int count, int per_wave, LdsCodes& L
 // The two-restarts-per-lane variant of run_segment for short product kinds.
 template <int KIND, int KMAX, bool UW, class AT>
 __device__ __forceinline__ void run_segment_r2(const ProblemDev& P, const Segment& S, const float* xs, AT* gs,
-                                               ObjAcc& facc, float gsc, float fsc, int tid, int logT, int* ctr) {
+                                               ObjAcc& facc, float gsc, float fsc, int logT, int* ctr) {
   constexpr int J = KMAX;
   constexpr int U = J <= 4 ? 2 : 1;
-  asm volatile("" : "+v"(tid));
-  const int lane = tid & (kWave - 1);
+  const int lane = lane_id();
   const int t2 = lane & ((1 << (logT - 1)) - 1);
   const int sub = lane >> (logT - 1);
   const int per_wave = kWave >> (logT - 1);
@@ -1252,15 +1011,15 @@ struct StatsOut {
 
 template <int KIND, int KMAX, int MAXB, class AT, bool ST = false, bool CL = false>
 __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& S, const float* xs, AT* gs,
-                                            ObjAcc& facc, float gsc, float fsc, int tid, int logT, int* ctr,
+                                            ObjAcc& facc, float gsc, float fsc, int logT, int* ctr,
                                             LdsCodes& L, StatsOut so = {}) {
   if constexpr (!ST && (KIND == KIND_PROD1 || KIND == KIND_PROD2) && MAXB <= kMaxbShort && KMAX <= 8) {
     if (!CL && logT >= 1) {
       // unit weights (a problem-wide flag): no weight fetch or multiply
       if (P.unit_weights)
-        run_segment_r2<KIND, KMAX, true>(P, S, xs, gs, facc, gsc, fsc, tid, logT, ctr);
+        run_segment_r2<KIND, KMAX, true>(P, S, xs, gs, facc, gsc, fsc, logT, ctr);
       else
-        run_segment_r2<KIND, KMAX, false>(P, S, xs, gs, facc, gsc, fsc, tid, logT, ctr);
+        run_segment_r2<KIND, KMAX, false>(P, S, xs, gs, facc, gsc, fsc, logT, ctr);
       return;
     }
   }
@@ -1268,10 +1027,7 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
   constexpr int LG = Log2<G>::v;
   constexpr int J = KMAX / G;
   constexpr int U = CL ? 1 : pairs_per_lane<KIND, J, MAXB>();
-  // keep the lane-index arithmetic inside the segment: hoisting it out of the
-  // step loop for every instantiation at once exhausts the register budget
-  asm volatile("" : "+v"(tid));
-  const int lane = tid & (kWave - 1);
+  const int lane = lane_id();
   const int t = lane & ((1 << logT) - 1);
   const int lig = (lane >> logT) & (G - 1);
   const int sub = lane >> (logT + LG);
@@ -1305,7 +1061,7 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
         if constexpr (KIND == KIND_DFT) {
           dft_pair<KMAX, G>(P, S.z_off, f, lig, t, logT, xs, sink, fchunk, gsc, fsc);
         } else if constexpr (KIND == KIND_THR) {
-          thr_pair<KMAX, G>(f, lig, t, logT, xs, sink, fchunk, gsc, fsc);
+          window_pair<KMAX, G, true>(P, 0, f, lig, t, logT, xs, sink, fchunk, gsc, fsc);
         } else if constexpr (KIND == KIND_PMF && KMAX > 8) {
           // lanes take turns by class (the first remaining lane's class each
           // round; one round for a class-uniform chunk), so the class record and
@@ -1313,11 +1069,7 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
           for (;;) {
             const int cc = __builtin_amdgcn_readfirstlane(f.cls);
             if (f.cls == cc) {
-              if constexpr (G == 8) {
-                pmfg8_pair<KMAX>(P, cc, f, lig, t, logT, xs, sink, fchunk, gsc, fsc);
-              } else {
-                pmfg_pair<KMAX, G>(P, cc, f, lig, t, logT, xs, sink, fchunk, gsc, fsc);
-              }
+              window_pair<KMAX, G, false>(P, cc, f, lig, t, logT, xs, sink, fchunk, gsc, fsc);
               break;
             }
           }
@@ -1360,7 +1112,7 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
     }
     facc.own += fixed_term(fchunk);
   };
-  constexpr bool kHeavy = KIND == KIND_DFT || (KIND == KIND_THR && KMAX > 16) || (KIND == KIND_PMF && KMAX > 8);
+  constexpr bool kHeavy = KIND == KIND_DFT || KIND == KIND_THR || (KIND == KIND_PMF && KMAX > 16);
   if constexpr (CL)
     deal_chunks<FetchedU<J, U>>(S.c_count, per_wave, L, fetch, eval);
   else
@@ -1399,8 +1151,6 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
 
 #define PCLS_PMF_BUCKET_CASES(KIND, X) \
   PCLS_SHORT_BUCKET_CASES(KIND, X)       \
-  X(KIND, 8, 12)                         \
-  X(KIND, 9, 16)                         \
   X(KIND, 10, 24)                        \
   X(KIND, 11, 32)                        \
   X(KIND, 12, 48)
@@ -1415,13 +1165,12 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
 
 #define PCLS_CASE(KIND, B, KMAX)                                                                    \
   case (KIND)*kNumBuckets + (B):                                                                    \
-    if constexpr ((B) <= MAXB) run_segment<KIND, KMAX, MAXB, AT, ST, CL>(P, S, xs, gs, facc, gsc, fsc, tid, logT, ctr, L, so); \
+    if constexpr ((B) <= MAXB) run_segment<KIND, KMAX, MAXB, AT, ST, CL>(P, S, xs, gs, facc, gsc, fsc, logT, ctr, L, so); \
     break;
 
 template <int MAXB, class AT, bool ST = false, bool CL = false>
 __device__ __forceinline__ void run_any_segment(const ProblemDev& P, const Segment& S, const float* xs, AT* gs,
-                                                ObjAcc& facc, float gsc, float fsc, int tid, int logT,
-                                                int* ctr, LdsCodes& L, StatsOut so = {}) {
+                                                ObjAcc& facc, float gsc, float fsc, int logT, int* ctr, LdsCodes& L, StatsOut so = {}) {
   switch (S.kind * kNumBuckets + S.bucket) {
     PCLS_BUCKET_CASES(KIND_PROD1, PCLS_CASE)
     PCLS_BUCKET_CASES(KIND_PROD2, PCLS_CASE)
@@ -1653,12 +1402,12 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
       L.worked = false;
       for (int sg = 0; sg < n_seg; ++sg) {
         const Segment S = sg == 0 ? S0 : load_segment(P, sg);
-        run_any_segment<MAXB, AT, false, CL>(P, S, xs, gs, facc, A.gsc, A.fsc, tid, logT, nullptr, L);
+        run_any_segment<MAXB, AT, false, CL>(P, S, xs, gs, facc, A.gsc, A.fsc, logT, nullptr, L);
       }
     } else {
       for (int sg = 0; sg < n_seg; ++sg) {
         const Segment S = load_segment(P, sg);
-        run_any_segment<MAXB, AT, false, CL>(P, S, xs, gs, facc, A.gsc, A.fsc, tid, logT, ctr + sg, L);
+        run_any_segment<MAXB, AT, false, CL>(P, S, xs, gs, facc, A.gsc, A.fsc, logT, ctr + sg, L);
       }
     }
     if constexpr (!kDefer) deposit(facc, set_of(0));
@@ -1799,7 +1548,7 @@ __global__ void __launch_bounds__(1024) stats_kernel(ProblemDev P, const float* 
   LdsCodes L{};
   for (int sg = 0; sg < P.n_segments; ++sg) {
     const Segment S = load_segment(P, sg);
-    run_any_segment<MAXB, unsigned int, true>(P, S, xs, nullptr, facc, 1.f, 0.f, (int)threadIdx.x, 0, ctr + sg, L, so);
+    run_any_segment<MAXB, unsigned int, true>(P, S, xs, nullptr, facc, 1.f, 0.f, 0, ctr + sg, L, so);
   }
 }
 

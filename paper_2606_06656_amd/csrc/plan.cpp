@@ -454,6 +454,8 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
         C.c1 = d0;
         C.c0 = (float)(h > 0.f ? sp[(size_t)k] : sp[0]);
       }
+      // windows of up to 16 literals: one lane without nodes (the DFT kind) is faster
+      if (C.kind == KIND_PMF && k > kPmfMaxK && kBucketKmax[bucket_of(k, P->bucket_table)] <= 16) C.kind = KIND_DFT;
       if (C.kind == KIND_DFT) {
         const int kmax = kBucketKmax[bucket_of(k, P->bucket_table)];
         dft_class(sp, kmax, roots(kmax), C, P->nodes);
@@ -469,16 +471,12 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
         C.n_nodes = 1;
         P->nodes.push_back(N);
       } else if (C.kind == KIND_PMF) {
-        // lane-group PMF: d_0..d_31, h, threshold flag, in five node records
+        // lane-group PMF: d_0..d_31, h, in five node records
         float rec[40] = {};
         float h;
         const int w = pmf_window(sp, rec, &h, 32);
         C.window = w;
         rec[32] = h;
-        bool thr = true;  // d constant on the window
-        for (int c = 1; c < w; ++c)
-          if (rec[c] != rec[0]) thr = false;
-        rec[33] = thr ? 1.f : 0.f;
         C.c0 = (float)(h > 0.f ? sp[k] : sp[0]);
         C.node_off = (int32_t)P->nodes.size();
         C.n_nodes = 5;
