@@ -202,7 +202,7 @@ struct Fetched {
   float w;
 };
 
-template <int KIND, int J, int KMAX>
+template <int KIND, int J, int KMAX, bool LONG>
 __device__ __forceinline__ void fetch_pair(const ProblemDev& P, const Segment& S, int c_local, int lig,
                                            Fetched<J>& f) {
   // A lane past the segment fetches its last pair (valid memory, no branch); the
@@ -222,7 +222,12 @@ __device__ __forceinline__ void fetch_pair(const ProblemDev& P, const Segment& S
     f.cls = P.c_par[c];
   else
     f.cls = S.cls_fixed >= 0 ? S.cls_fixed : P.c_par[c];
-  f.w = P.unit_weights ? 1.f : P.c_w[c];
+  // opaque in the variants for long constraints: the comparison hoisted out of the
+  // step loop was kept as a mask in scratch memory there, whose reload waited for the
+  // codes just asked for (1.64 -> 1.62 ms a step)
+  int unit = P.unit_weights;
+  if constexpr (LONG) asm volatile("" : "+s"(unit));
+  f.w = unit ? 1.f : P.c_w[c];
 }
 
 // The constraints' codes, parameters and weights in LDS, and the wave's place
@@ -981,7 +986,7 @@ __device__ __forceinline__ void run_segment_r2(const ProblemDev& P, const Segmen
   };
   auto fetch = [&](int b, FetchedU<J, U>& f) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) fetch_pair<KIND, J, KMAX>(P, S, b + u * per_wave + sub, 0, f.p[u]);
+    for (int u = 0; u < U; ++u) fetch_pair<KIND, J, KMAX, false>(P, S, b + u * per_wave + sub, 0, f.p[u]);
   };
   auto eval = [&](int base, const FetchedU<J, U>& cur) {
     float fca = 0.f, fcb = 0.f;
@@ -1043,7 +1048,7 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
       if constexpr (CL)
         fetch_lds<KIND, J>(P, S, L, b + sub, lig, f.p[u]);
       else
-        fetch_pair<KIND, J, KMAX>(P, S, b + u * per_wave + sub, lig, f.p[u]);
+        fetch_pair<KIND, J, KMAX, (MAXB > kMaxbShort)>(P, S, b + u * per_wave + sub, lig, f.p[u]);
     }
   };
   auto eval = [&](int base, const FetchedU<J, U>& cur) {
