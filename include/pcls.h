@@ -166,6 +166,15 @@ int32_t pcls_init_restarts_masked(const pcls_problem* p, int32_t R, uint64_t see
                                   float* d_x, void* hip_stream);
 
 /*
+ * State from rows of restarts: d_x[v][r] = d_rows[r][v], padding columns 0.
+ *   d_rows    : device [R][n] float32, row-major, read only.
+ *   d_outside : device int32 or NULL: 1 if any entry is not within [-1, 1] (NaN
+ *               included), else 0.
+ */
+int32_t pcls_state_from_rows(const pcls_problem* p, int32_t R, const float* d_rows, float* d_x, int32_t* d_outside,
+                             void* hip_stream);
+
+/*
  * Objective and gradient at X (Background, "Satisfaction as Optimisation").
  *   d_x    : device [n][R_pad] float32, read only.
  *   d_obj  : device [R] float32, F_r = sum_c w_c FE_c(x_r).

@@ -26,13 +26,23 @@ class FEObjective(torch.autograd.Function):
             raise ValueError(f"x must be (R, {problem.n}), got {tuple(x.shape)}")
         if x.device != problem.device:
             raise ValueError("x must live on the problem's device")
-        if not bool(torch.all(x.detach().abs() <= 1)):
+        R = x.shape[0]
+        rows = x.detach()
+        if rows.dtype == torch.float32 and rows.is_contiguous() and R > 0:
+            # the range check rides along with the transposition and is read after the
+            # evaluation has been launched: the host waits once, not before the work
+            X, outside = problem.state_and_range(rows)
+            obj, grad = problem.evaluate(X, R, want_grad=ctx.needs_input_grad[0])
+            inside = not bool(outside.item())
+        else:
+            inside = bool(torch.all(rows.abs() <= 1))
+            if inside:
+                X = problem.new_state(R)
+                X[:, :R] = rows.to(torch.float32).T
+                obj, grad = problem.evaluate(X, R, want_grad=ctx.needs_input_grad[0])
+        if not inside:
             raise ValueError("x must lie in [-1, 1]^n (the cube the objective and its fixed-point scales are "
                              "defined on)")
-        R = x.shape[0]
-        X = problem.new_state(R)
-        X[:, :R] = x.detach().to(torch.float32).T
-        obj, grad = problem.evaluate(X, R, want_grad=ctx.needs_input_grad[0])
         if grad is not None:
             ctx.save_for_backward(grad[:, :R])
         ctx.in_dtype = x.dtype

@@ -1748,6 +1748,31 @@ __global__ void __launch_bounds__(256) init_kernel(float* __restrict__ X, int n,
   }
 }
 
+// Rows of restarts [R][n] to the state layout [n][ldx] (padding columns 0), through
+// a 64 x 64 tile in LDS; sets *outside to 1 if an entry is not within [-1, 1].
+__global__ void __launch_bounds__(256) state_rows_kernel(const float* __restrict__ rows, int n, int R, int ldx,
+                                                         float* __restrict__ X, int32_t* __restrict__ outside) {
+  __shared__ float tile[64][65];
+  const int r0 = blockIdx.x * 64, v0 = blockIdx.y * 64;
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+  bool bad = false;
+#pragma unroll 4
+  for (int q = ty; q < 64; q += 4) {
+    const int r = r0 + q, v = v0 + tx;
+    float x = 0.f;
+    if (r < R && v < n) x = rows[(size_t)r * n + v];
+    bad |= !(fabsf(x) <= 1.f);
+    tile[q][tx] = x;
+  }
+  __syncthreads();
+#pragma unroll 4
+  for (int q = ty; q < 64; q += 4) {
+    const int v = v0 + q, r = r0 + tx;
+    if (v < n && r < ldx) X[(size_t)v * ldx + r] = tile[tx][q];
+  }
+  if (outside && __any(bad) && tx == 0) *outside = 1;
+}
+
 // ---------------------------------------------------------------- extract
 
 __global__ void fill_i32_kernel(int32_t* p, int32_t v, int count) {
@@ -2568,6 +2593,26 @@ int32_t pcls_init_restarts_masked(const pcls_problem* p, int32_t R, uint64_t see
                      d_x, p->n, R, R_pad,
                      (uint32_t)seed, (uint32_t)(seed >> 32), d_mask);
   PCLS_HIP(hipGetLastError(), "init_kernel launch");
+  clear_error();
+  return PCLS_OK;
+}
+
+int32_t pcls_state_from_rows(const pcls_problem* p, int32_t R, const float* d_rows, float* d_x, int32_t* d_outside,
+                             void* stream) {
+  int32_t st = check_bound(p);
+  if (st != PCLS_OK) return st;
+  if (R < 0) return set_error(PCLS_E_INVALID, "R must be >= 0");
+  if (R == 0) return PCLS_OK;
+  if (!d_rows || !d_x) return set_error(PCLS_E_INVALID, "d_rows and d_x must not be NULL");
+  const int R_pad = round_up64(R);
+  hipStream_t s = (hipStream_t)stream;
+  if (d_outside) {
+    hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, s, d_outside, 0, 1);
+    PCLS_HIP(hipGetLastError(), "fill launch");
+  }
+  hipLaunchKernelGGL(state_rows_kernel, dim3(R_pad / 64, (p->n + 63) / 64), dim3(256), 0, s, d_rows, p->n, R, R_pad, d_x,
+                     d_outside);
+  PCLS_HIP(hipGetLastError(), "state_rows launch");
   clear_error();
   return PCLS_OK;
 }

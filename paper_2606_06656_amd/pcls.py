@@ -23,7 +23,7 @@ STATUS_NAMES = {0: "PCLS_OK", 1: "PCLS_E_INVALID", 2: "PCLS_E_UNSUPPORTED", 3: "
 # exported entry points (checked by the CPU test suite against include/pcls.h)
 EXPORTS = ["pcls_plan", "pcls_plan_ex", "pcls_problem_info", "pcls_upload", "pcls_init_restarts",
            "pcls_init_restarts_masked",
-           "pcls_evaluate", "pcls_step", "pcls_step_ex", "pcls_extract", "pcls_set_launch", "pcls_launch_info",
+           "pcls_state_from_rows", "pcls_evaluate", "pcls_step", "pcls_step_ex", "pcls_extract", "pcls_set_launch", "pcls_launch_info",
            "pcls_destroy", "pcls_last_error",
            "pcls_batch_create", "pcls_batch_bind", "pcls_batch_set_config", "pcls_batch_get_config",
            "pcls_batch_step", "pcls_batch_capture", "pcls_batch_replay", "pcls_batch_autotune",
@@ -84,6 +84,8 @@ def load_library():
     L.pcls_init_restarts.argtypes = [P, i32, u64, vp, vp]
     L.pcls_init_restarts_masked.restype = i32
     L.pcls_init_restarts_masked.argtypes = [P, i32, u64, vp, vp, vp]
+    L.pcls_state_from_rows.restype = i32
+    L.pcls_state_from_rows.argtypes = [P, i32, vp, vp, vp, vp]
     L.pcls_evaluate.restype = i32
     L.pcls_evaluate.argtypes = [P, i32, vp, vp, vp, vp]
     L.pcls_step.restype = i32
@@ -229,6 +231,18 @@ class Problem(Plan):
         X = self.new_state(R)
         X[:, :R] = x.to(self.device).T
         return X
+
+    def state_and_range(self, x):
+        """(n, R_pad) state of contiguous float32 device rows x (R, n), and a device
+        int32 that is 1 if an entry is not within [-1, 1] (one kernel, no host wait)."""
+        import torch
+        R = x.shape[0]
+        if x.dtype != torch.float32 or not x.is_contiguous() or tuple(x.shape) != (R, self.n) or x.device != self.device:
+            raise PclsError(PCLS_E_INVALID, "rows must be a contiguous float32 (R, n) tensor on the problem's device")
+        X = torch.empty((self.n, round_up64(R)), dtype=torch.float32, device=self.device)
+        outside = torch.empty(1, dtype=torch.int32, device=self.device)
+        check(load_library().pcls_state_from_rows(self.handle, R, _tptr(x), _tptr(X), _tptr(outside), _stream()))
+        return X, outside
 
     def _check_state(self, X, R):
         import torch
