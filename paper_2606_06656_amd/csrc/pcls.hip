@@ -1255,7 +1255,7 @@ __device__ __forceinline__ Segment load_segment(const ProblemDev& P, int sg) {
 //      odd restarts of two-restart lanes when T >= 2; the long-constraint
 //      variants use slot t of set 0 for restart t) |
 //      one work counter per segment | per restart: converged flag, max |dx| |
-//      CL: literal codes, one word a constraint, weights unless all 1.
+//      CL: literal codes, one word a constraint, weights unless all 1, held values.
 template <int MAXB, class AT, int LT = -1, bool CL = false>
 __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArgs& A, unsigned long long* lds_raw) {
   static_assert(!CL || LT == 0, "codes in LDS: one restart a tile");
@@ -1299,6 +1299,7 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
   }
   if (tid < n_seg) ctr[tid] = 0;
   LdsCodes L{};
+  int8_t* fixed = nullptr;  // CL: A.fixed in LDS
   if constexpr (CL) {
     const int n4 = (P.n_codes + 3) / 4;
     int4* lit = reinterpret_cast<int4*>(((uintptr_t)(dxmax + T) + 15) & ~(uintptr_t)15);
@@ -1312,6 +1313,10 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
     for (int i = tid; i < P.m; i += nth) {
       par[i] = P.c_par[i];
       if (!P.unit_weights) w[i] = P.c_w[i];
+    }
+    if (A.fixed) {
+      fixed = reinterpret_cast<int8_t*>(w + (P.unit_weights ? 0 : P.m));
+      for (int i = tid; i < P.n; i += nth) fixed[i] = A.fixed[i];
     }
     L = {reinterpret_cast<int*>(lit), par, w, __builtin_amdgcn_readfirstlane(tid >> 6), nth >> 6, 0, false};
   }
@@ -1388,6 +1393,7 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
   // claims fewer chunks).  Long-constraint variants reduce within the step.
   constexpr bool kDefer = MAXB <= kMaxbShort;
   ObjAcc prev{0, 0, 0};
+  bool converged = false;  // LT == 0
   int done = A.n_steps;  // steps taken (fewer once every restart has converged)
 
   Segment S0{};
@@ -1425,6 +1431,7 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
     } else {
       prev = facc;
     }
+    if (LT == 0 && A.tol > 0.f && owner) dxmax[-((s + 1) & 1)] = 0u;  // of step s + 1
     if (eval) {
       if (A.g_out) {
         for (int i = tid; i < NT; i += nth) {
@@ -1459,18 +1466,34 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
         const int v = i >> logT;
         float xn = fmaf(-lr, FixedAcc<AT>::value(grad_word(i), A.ginv, P.occ[v]), xs[i]);
         xn = fminf(1.f, fmaxf(-1.f, xn));
-        if (A.fixed && A.fixed[v] != 0) xn = (float)A.fixed[v];
+        if (A.fixed) {
+          const int8_t f = CL ? fixed[v] : A.fixed[v];
+          if (f != 0) xn = (float)f;
+        }
         dmax = fmaxf(dmax, fabsf(xn - xs[i]));
         xs[i] = xn;
         gs[i] = 0;
       }
       if (A.tol > 0.f) {
         for (int o = T; o < kWave; o <<= 1) dmax = fmaxf(dmax, __shfl_xor(dmax, o));
-        if ((tid & (kWave - 1)) < T) atomicMax(&dxmax[t], __float_as_uint(dmax));  // dmax >= 0: bits are monotone
+        // dmax >= 0: bits are monotone
+        if ((tid & (kWave - 1)) < T) atomicMax(LT == 0 ? &dxmax[-(s & 1)] : &dxmax[t], __float_as_uint(dmax));
       }
     }
     __syncthreads();
-    if (!eval && A.tol > 0.f) {
+    if (LT == 0 && !eval && A.tol > 0.f) {
+      // one restart: every thread reads its largest change and decides alone, with no
+      // further barrier (the two words alternate; the one of step s - 1, read before
+      // this step's first barrier, was cleared after it)
+      if (__uint_as_float(dxmax[-(s & 1)]) < A.tol) {
+        if (owner) {
+          if (A.iters && r0 + ot < A.R) A.iters[r0 + ot] = s + 1;
+        }
+        converged = true;
+        done = s + 1;
+        break;
+      }
+    } else if (!eval && A.tol > 0.f) {
       // convergence: a tile stops once every restart in it has converged
       if (owner) {
         const int r = r0 + ot;
@@ -1501,7 +1524,8 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
   // a tile that stopped early repeats its last objective for the remaining steps
   if (owner && A.trace && r0 + ot < A.R)
     for (int q = done; q < A.n_steps; ++q) A.trace[(size_t)q * A.R + r0 + ot] = F_last;
-  if (!eval && A.tol > 0.f && A.iters && owner && r0 + ot < A.R && !conv[ot]) A.iters[r0 + ot] = A.n_steps;
+  if (!eval && A.tol > 0.f && A.iters && owner && r0 + ot < A.R && !(LT == 0 ? converged : conv[ot] != 0))
+    A.iters[r0 + ot] = A.n_steps;
   if (!eval) {
     for (int i = tid; i < NT; i += nth) {
       const int v = i >> logT, tt = i & (T - 1);
@@ -2148,7 +2172,7 @@ bool auto_acc64(const pcls_problem* p, size_t cap) {
 // against 4.77; copying costs up to about 3 us.
 constexpr int kSmallSteps = 8;
 size_t codes_lds_bytes(const pcls_problem* p) {
-  return 16 + 4 * ((p->litT.size() + 3) / 4 * 4 + (size_t)p->m * (p->unit_weights ? 1 : 2));
+  return 16 + 4 * ((p->litT.size() + 3) / 4 * 4 + (size_t)p->m * (p->unit_weights ? 1 : 2)) + ((size_t)p->n + 3) / 4 * 4;
 }
 
 // steps: of the launch; 0 for an evaluation
