@@ -1281,12 +1281,24 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
   const bool owner = CL ? tid == nth - kWave : tid < T;
   const int ot = CL ? 0 : tid;
 
-  for (int i = tid; i < NT; i += nth) {
-    const int v = i >> logT, tt = i & (T - 1);
-    float x = A.X[(size_t)v * ldx + r0 + tt];
-    if (A.fixed && A.fixed[v] != 0) x = (float)A.fixed[v];
-    xs[i] = x;
-    gs[i] = 0;
+  // eight loads in flight a thread: one at a time, the tile's column took a memory
+  // latency per element and thread
+  constexpr int kLoads = 8;
+  for (int i0 = tid; i0 < NT; i0 += kLoads * nth) {
+    float x[kLoads];
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+      const int i = min(i0 + u * nth, NT - 1), v = i >> logT, tt = i & (T - 1);
+      x[u] = A.X[(size_t)v * ldx + r0 + tt];
+    }
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+      const int i = i0 + u * nth;
+      if (i >= NT) break;
+      if (A.fixed && A.fixed[i >> logT] != 0) x[u] = (float)A.fixed[i >> logT];
+      xs[i] = x[u];
+      gs[i] = 0;
+    }
   }
   for (int i = NT + tid; i < NR; i += nth) {  // pad rows: x = +1, never stepped
     xs[i] = 1.f;
@@ -1554,7 +1566,12 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
 template <int MAXB, class AT, int LT, bool CL>
 __global__ void __launch_bounds__(1024) tile_kernel(ProblemDev P, TileArgs A) {
   extern __shared__ __attribute__((aligned(16))) unsigned long long lds_raw[];  // 16 B: vector LDS accesses
-  A.r0 = blockIdx.x << (LT >= 0 ? LT : A.logT);
+  // Workgroups go to the eight XCDs in turn.  Within each 256 of them, an XCD's 32
+  // take neighbouring tiles: at one restart a tile its 32 columns share every 128-byte
+  // line of X, which then passes through one L2 instead of eight.
+  unsigned tile = blockIdx.x;
+  if ((tile | 255u) < gridDim.x) tile = (tile & ~255u) | ((tile & 7u) << 5) | ((tile >> 3) & 31u);
+  A.r0 = (int)tile << (LT >= 0 ? LT : A.logT);
   resident_tile<MAXB, AT, LT, CL>(P, A, lds_raw);
 }
 
