@@ -95,10 +95,12 @@ typedef struct pcls_info {
   int32_t block_threads;     /* threads per workgroup of the resident engine (0 = auto) */
   size_t workspace_bytes;
   size_t lds_bytes_per_restart; /* on-chip bytes one restart's state needs */
-  int32_t cons_by_kind[5];   /* constraints per evaluation path: one-node product, two-node
-                                product, K-node DFT, truncated count distribution (k <= 48,
-                                window of at most 4 counts for k <= 8, at most half the
-                                length bucket above), constant */
+  int32_t cons_by_kind[5];   /* constraints by spectrum: one-node product, two-node product,
+                                general (inverse DFT of the count distribution), constant
+                                outside a window of counts at one end (k <= 48, window of at
+                                most 4 counts for k <= 8, at most half the length bucket
+                                above), constant.  Thresholds of 9 to 64 literals run on a
+                                kernel of their own and count in the third or fourth entry */
   int32_t bucket_table;      /* length-bucket table of the plan (pcls_plan_options) */
 } pcls_info;
 

@@ -1012,6 +1012,7 @@ __device__ __forceinline__ void run_segment_r2(const ProblemDev& P, const Segmen
 struct StatsOut {
   unsigned long long* acc;
   float scale;
+  int live;  // restarts of the tile (the others read padding and count nothing)
 };
 
 template <int KIND, int KMAX, int MAXB, class AT, bool ST = false, bool CL = false>
@@ -1107,7 +1108,10 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
           sq = sk.acc;
         }
         for (int o = 1 << logT; o < (G << logT); o <<= 1) sq += __shfl_xor(sq, o);  // the pair's G lanes
-        if (valid && lig == 0) atomicAdd(&so.acc[S.c_begin + b_u + sub], (unsigned long long)fixed_term(sq * so.scale));
+        // the tile's restarts as integers (exact in any order), then one atomic
+        long long term = t < so.live ? fixed_term(sq * so.scale) : 0;
+        for (int o = 1; o < (1 << logT); o <<= 1) term += __shfl_xor(term, o);
+        if (valid && lig == 0 && t == 0) atomicAdd(&so.acc[S.c_begin + b_u + sub], (unsigned long long)term);
       } else {
         if (valid) {
           GradSink<AT, pair_words<MAXB, AT>()> sk{gs, logT >= 1 && (t & 1) == 0};
@@ -1576,25 +1580,31 @@ __global__ void __launch_bounds__(1024) tile_kernel(ProblemDev P, TileArgs A) {
 }
 
 // ---------------------------------------------------- constraint statistics
-// One workgroup per restart evaluates every constraint once and adds, per
+// One workgroup per tile of restarts evaluates every constraint once and adds, per
 // constraint, the sum over its literals of (dFE_c/dy_i)^2 (unweighted) into a
 // 64-bit fixed-point accumulator: exact integer sums, so the result does not
-// depend on the order in which restarts or waves arrive.
+// depend on the tiles or on the order in which restarts or waves arrive.  Bound by
+// the atomics that all XCDs send to the same addresses and by latency; T restarts
+// a tile send one atomic for T (n 5000, 10000 constraints, R 512: T = 1 121 us,
+// T = 2 117 us).
 template <int MAXB>
-__global__ void __launch_bounds__(1024) stats_kernel(ProblemDev P, const float* __restrict__ X, int ldx,
+__global__ void __launch_bounds__(1024) stats_kernel(ProblemDev P, const float* __restrict__ X, int R, int ldx, int logT,
                                                      StatsOut so) {
   extern __shared__ __attribute__((aligned(16))) unsigned long long lds_raw[];  // 16 B: vector LDS accesses
   float* xs = reinterpret_cast<float*>(lds_raw);
-  int* ctr = reinterpret_cast<int*>(xs + ((P.n + P.n_pad + 1) & ~1));
-  const int r = blockIdx.x;
-  for (int i = threadIdx.x; i < P.n + P.n_pad; i += blockDim.x) xs[i] = i < P.n ? X[(size_t)i * ldx + r] : 1.f;
+  const int T = 1 << logT, NT = P.n << logT, rows = (P.n + P.n_pad) << logT;
+  int* ctr = reinterpret_cast<int*>(xs + ((rows + 1) & ~1));
+  const int r0 = (int)blockIdx.x << logT;
+  for (int i = threadIdx.x; i < rows; i += blockDim.x)
+    xs[i] = i < NT ? X[(size_t)(i >> logT) * ldx + r0 + (i & (T - 1))] : 1.f;
   if ((int)threadIdx.x < P.n_segments) ctr[threadIdx.x] = 0;
+  so.live = R - r0;
   __syncthreads();
   ObjAcc facc{0, 0, 0};
   LdsCodes L{};
   for (int sg = 0; sg < P.n_segments; ++sg) {
     const Segment S = load_segment(P, sg);
-    run_any_segment<MAXB, unsigned int, true>(P, S, xs, nullptr, facc, 1.f, 0.f, 0, ctr + sg, L, so);
+    run_any_segment<MAXB, unsigned int, true>(P, S, xs, nullptr, facc, 1.f, 0.f, logT, ctr + sg, L, so);
   }
 }
 
@@ -1695,7 +1705,7 @@ __global__ void __launch_bounds__(1024) batch_kernel(const BatchInst* __restrict
 template __global__ void batch_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC>(const BatchInst*, const BatchItem*, int,
                                                                            unsigned int*, float, int, int);
 #elif PCLS_VARIANT_LT == -3
-template __global__ void stats_kernel<PCLS_VARIANT_MAXB>(ProblemDev, const float*, int, StatsOut);
+template __global__ void stats_kernel<PCLS_VARIANT_MAXB>(ProblemDev, const float*, int, int, int, StatsOut);
 #elif PCLS_VARIANT_LT == -4
 template __global__ void tile_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC, 0, true>(ProblemDev, TileArgs);
 #else
@@ -1717,7 +1727,7 @@ template __global__ void tile_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC, PCLS_V
                                                                    unsigned int*, float, int, int);                \
   extern template __global__ void batch_kernel<MAXB, unsigned long long>(const BatchInst*, const BatchItem*, int,  \
                                                                          unsigned int*, float, int, int);          \
-  extern template __global__ void stats_kernel<MAXB>(ProblemDev, const float*, int, StatsOut);
+  extern template __global__ void stats_kernel<MAXB>(ProblemDev, const float*, int, int, int, StatsOut);
 PCLS_EXTERN_VARIANT(kMaxbShort)
 PCLS_EXTERN_VARIANT(kMaxbMid)
 PCLS_EXTERN_VARIANT(kMaxbAll)
@@ -2467,25 +2477,32 @@ int32_t batch_attrs() {
 
 // Launches of the per-constraint gradient statistic: zero the accumulator
 // (a fill kernel, not a memset node, so the launches can be captured), one
-// workgroup per restart, then the conversion to float in the caller's order.
+// workgroup per tile of restarts, then the conversion to float in the caller's order.
 int32_t grad_stats_launch(const pcls_problem* p, int32_t R, const float* d_x, unsigned long long* d_acc,
                           float* d_out, hipStream_t s) {
   DeviceLimits lim;
   int32_t st = device_limits(lim);
   if (st != PCLS_OK) return st;
-  const size_t lds = (size_t)((state_rows(p) + 1) & ~1) * 4 + 4 * kMaxSegments;
-  if (lds > (size_t)lim.lds_max)
+  auto lds_bytes = [&](int logT) { return ((((size_t)state_rows(p) << logT) + 1) & ~(size_t)1) * 4 + 4 * kMaxSegments; };
+  if (lds_bytes(0) > (size_t)lim.lds_max)
     return set_error(PCLS_E_UNSUPPORTED, "state of %d variables does not fit in LDS", p->n);
+  // as many restarts a tile as fit while every CU still has a tile
+  int logT = 0;
+  while (logT < 3 && (2 << logT) * p->max_group <= kWave && (R >> (logT + 1)) >= lim.n_cu &&
+         lds_bytes(logT + 1) <= (size_t)lim.lds_max)
+    ++logT;
+  const size_t lds = lds_bytes(logT);
   // every term is at most 1, so a constraint's sum over R restarts is at most R k
   const int bits = (int)std::ceil(std::log2((double)R * (double)std::max(1, p->max_k) + 1.0));
   const int sc = std::min(40, 60 - bits);
   hipLaunchKernelGGL(fill_u32_kernel, dim3((2 * p->m + 255) / 256), dim3(256), 0, s, (unsigned int*)d_acc, 0u,
                      2 * p->m);
   PCLS_HIP(hipGetLastError(), "fill launch");
-  StatsOut so{d_acc, std::ldexp(1.0f, sc)};
-  const int block = p->n > 4096 ? 1024 : 256;
+  StatsOut so{d_acc, std::ldexp(1.0f, sc), 0};
+  const int block = ((int64_t)p->n << logT) > 4096 ? 1024 : 256;
   auto kern = p->max_bucket <= kMaxbShort ? stats_kernel<kMaxbShort> : (p->max_bucket <= kMaxbMid ? stats_kernel<kMaxbMid> : stats_kernel<kMaxbAll>);
-  hipLaunchKernelGGL(kern, dim3(R), dim3(block), lds, s, p->dev, d_x, round_up64(R), so);
+  hipLaunchKernelGGL(kern, dim3((R + (1 << logT) - 1) >> logT), dim3(block), lds, s, p->dev, d_x, R, round_up64(R),
+                     logT, so);
   PCLS_HIP(hipGetLastError(), "stats_kernel launch");
   hipLaunchKernelGGL(stats_finish_kernel, dim3((p->m + 255) / 256), dim3(256), 0, s, d_acc, p->dev.perm, p->m,
                      std::ldexp(1.0, -sc), d_out);
