@@ -1,6 +1,7 @@
-// The whole message-passing network in a few launches: forward (two kernels of
-// embedding, two per round) and backward (one of the head, two per round, one of
-// the constraint embedding, two for the weight gradients).  Same arithmetic as
+// The whole message-passing network in a few launches: forward (one of both
+// embeddings, two per round) and backward (one of the head, two per round, the
+// last with the constraint embedding, two for the weight gradients).  Same
+// arithmetic as
 // the single kernels of mpnn.hip: activations and output gradients enter the
 // bf16 matrix products as two bf16 parts, weight gradients as three of the four
 // cross products; the forward pass is the same operation by operation, so its
@@ -226,7 +227,14 @@ struct EmbedArgs {
   float* P;
 };
 
-__global__ void __launch_bounds__(256) embed_kernel(EmbedArgs A) {
+// Two sides that do not wait for each other share a launch: the first blocks0
+// blocks take V, the rest C (embedding and last backward launch: a launch of few
+// blocks costs its latency whatever it does: predict 8 x 2000 variables 151 -> 149 us,
+// training 16 x 200 222 -> 213 us, with the two-step meeting of wgrad_kernel's waves).
+__global__ void __launch_bounds__(256) embed_kernel(EmbedArgs V, int blocks0, EmbedArgs C) {
+  const bool second = (int)blockIdx.x >= blocks0;
+  const EmbedArgs A = second ? C : V;
+  const int block = blockIdx.x - (second ? blocks0 : 0), blocks = second ? gridDim.x - blocks0 : blocks0;
   __shared__ __attribute__((aligned(16))) __bf16 we[64 * (kFeat + 8)], wn[128 * (kHid + 8)];
   __shared__ __attribute__((aligned(16))) float hs[4][16 * (kHid + 4)];
   Stage<64, kFeat, false> se;
@@ -238,7 +246,7 @@ __global__ void __launch_bounds__(256) embed_kernel(EmbedArgs A) {
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c4 = 4 * (lane & 15);
   const float4 b = *reinterpret_cast<const float4*>(A.e + c4);
-  for (int row0 = (blockIdx.x * 4 + wave) * 16; row0 < A.N; row0 += gridDim.x * 64) {
+  for (int row0 = (block * 4 + wave) * 16; row0 < A.N; row0 += blocks * 64) {
     Split f[1];
     load_rows<kFeat>(f, A.F, row0, A.N, lane);
     floatx4 acc[4] = {};
@@ -385,7 +393,11 @@ struct BackArgs {
   float* dZ;             // [N][64]
 };
 
-__global__ void __launch_bounds__(256) back_kernel(BackArgs A) {
+// blocks0 as in embed_kernel
+__global__ void __launch_bounds__(256) back_kernel(BackArgs V, int blocks0, BackArgs C) {
+  const bool second = (int)blockIdx.x >= blocks0;
+  const BackArgs A = second ? C : V;
+  const int block = blockIdx.x - (second ? blocks0 : 0), blocks = second ? gridDim.x - blocks0 : blocks0;
   __shared__ __attribute__((aligned(16))) __bf16 wb[64 * (128 + 8)], ws[64 * (kHid + 8)];
   __shared__ __attribute__((aligned(16))) float qs[4][16 * (128 + 4)];
   Stage<64, 128, true> sb;
@@ -394,7 +406,7 @@ __global__ void __launch_bounds__(256) back_kernel(BackArgs A) {
   if (A.dSelf) sw.load(A.Wself);
   bool staged = false;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c4 = 4 * (lane & 15);
-  for (int row0 = (blockIdx.x * 4 + wave) * 16;; row0 += gridDim.x * 64) {
+  for (int row0 = (block * 4 + wave) * 16;; row0 += blocks * 64) {
     floatx4 acc[4] = {};
     float4 p[4], n[4];
     if (A.In && row0 < A.N) gather4<true>(A.g, A.In, row0, A.N, lane, p, n);
@@ -520,20 +532,21 @@ __device__ __forceinline__ void grad_chunk(const Grad& G, int begin, int end, fl
     sum.z += __shfl_xor(sum.z, o);
     sum.w += __shfl_xor(sum.w, o);
   }
-  // the waves add their tiles one after another; element (m, k), m = 4 (row of the
-  // tile) + i, k = KT (lane % 16) + j
-  for (int w = 0; w < 4; ++w) {
-    if (wave == w) {
+  // waves 0 and 1 store their tiles, 2 and 3 add theirs, the store to memory adds the
+  // two; element (m, k), m = 4 (row of the tile) + i, k = KT (lane % 16) + j
+  float* half = lds + (wave & 1) * (64 * 64 + 64);
+  for (int w = 0; w < 2; ++w) {
+    if (wave >> 1 == w) {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          float* p = lds + (size_t)(4 * (4 * (lane >> 4) + e) + i) * K + KT * (lane & 15);
+          float* p = half + (size_t)(4 * (4 * (lane >> 4) + e) + i) * K + KT * (lane & 15);
 #pragma unroll
           for (int j = 0; j < KT; ++j) p[j] = w == 0 ? acc[i][j][e] : p[j] + acc[i][j][e];
         }
       if (lane < 16) {
-        float* p = lds + 64 * K + c4;
+        float* p = half + 64 * K + c4;
         p[0] = w == 0 ? sum.x : p[0] + sum.x;
         p[1] = w == 0 ? sum.y : p[1] + sum.y;
         p[2] = w == 0 ? sum.z : p[2] + sum.z;
@@ -542,11 +555,11 @@ __device__ __forceinline__ void grad_chunk(const Grad& G, int begin, int end, fl
     }
     __syncthreads();
   }
-  for (int i = threadIdx.x; i < 64 * K + 64; i += blockDim.x) out[i] = lds[i];
+  for (int i = threadIdx.x; i < 64 * K + 64; i += blockDim.x) out[i] = lds[i] + lds[64 * 64 + 64 + i];
 }
 
 __global__ void __launch_bounds__(256) wgrad_kernel(Grads A, float* __restrict__ partial) {
-  __shared__ __attribute__((aligned(16))) float lds[64 * 64 + 64];
+  __shared__ __attribute__((aligned(16))) float lds[2 * (64 * 64 + 64)];
   int q = 0;
   while (q + 1 < A.count && (int)blockIdx.x >= A.g[q + 1].block0) ++q;
   const Grad G = A.g[q];
@@ -673,14 +686,11 @@ int32_t pcls_mpnn_forward(const pcls_mpnn_graph* g, const float* params, const u
   hipStream_t s = (hipStream_t)stream;
   const int Nv = g->n_vars, Nc = g->n_cons;
   const Acts a = acts_of((size_t)Nv, (size_t)Nc);
-  if (Nv > 0) {
-    const EmbedArgs E{g->feat_v,       Nv, params_bf16 + kEv, params + kev, acts + a.hv[0], params_bf16 + layer_at(0, kWpn),
+  if (Nv > 0 || Nc > 0) {
+    const EmbedArgs V{g->feat_v,       Nv, params_bf16 + kEv, params + kev, acts + a.hv[0], params_bf16 + layer_at(0, kWpn),
                       acts + a.pm};
-    hipLaunchKernelGGL(embed_kernel, dim3(blocks_for(Nv)), dim3(256), 0, s, E);
-  }
-  if (Nc > 0) {
-    const EmbedArgs E{g->feat_c, Nc, params_bf16 + kEc, params + kec, acts + a.hc[0], nullptr, nullptr};
-    hipLaunchKernelGGL(embed_kernel, dim3(blocks_for(Nc)), dim3(256), 0, s, E);
+    const EmbedArgs C{g->feat_c, Nc, params_bf16 + kEc, params + kec, acts + a.hc[0], nullptr, nullptr};
+    hipLaunchKernelGGL(embed_kernel, dim3(blocks_for(Nv) + blocks_for(Nc)), dim3(256), 0, s, V, blocks_for(Nv), C);
   }
   for (int l = 0; l < kLayers; ++l) {
     const bool last = l + 1 == kLayers;
@@ -724,19 +734,18 @@ int32_t pcls_mpnn_backward(const pcls_mpnn_graph* g, const float* params, const 
       const BackArgs C{Nc, Csr{g->cptr, g->cidx, g->cw_t}, scratch + b.dzv[l + 1], params_bf16 + layer_at(l, kUpn),
                        scratch + b.dq[l], top ? nullptr : scratch + b.dzc[l + 2],
                        top ? nullptr : params_bf16 + layer_at(l + 1, kW1), acts + a.hc[l + 1], scratch + b.dzc[l + 1]};
-      hipLaunchKernelGGL(back_kernel, dim3(blocks_for(Nc)), dim3(256), 0, s, C);
+      hipLaunchKernelGGL(back_kernel, dim3(blocks_for(Nc)), dim3(256), 0, s, C, blocks_for(Nc), C);
     }
-    if (Nv > 0) {
+    if (Nv > 0 || (l == 0 && Nc > 0)) {
       const BackArgs V{Nv, Csr{g->vptr, g->vidx, g->vw_t}, scratch + b.dzc[l + 1], params_bf16 + layer_at(l, kWpn),
                        scratch + b.dp[l], scratch + b.dzv[l + 1], params_bf16 + layer_at(l, kW2), acts + a.hv[l],
                        scratch + b.dzv[l]};
-      hipLaunchKernelGGL(back_kernel, dim3(blocks_for(Nv)), dim3(256), 0, s, V);
+      // the constraint embedding's gradient needs no more than round 0's
+      const BackArgs C{Nc, Csr{nullptr, nullptr, nullptr}, nullptr, nullptr, nullptr, scratch + b.dzc[1],
+                       params_bf16 + layer_at(0, kW1), acts + a.hc[0], scratch + b.dzc[0]};
+      const int with = l == 0 ? blocks_for(Nc) : 0;
+      hipLaunchKernelGGL(back_kernel, dim3(blocks_for(Nv) + with), dim3(256), 0, s, V, blocks_for(Nv), C);
     }
-  }
-  if (Nc > 0) {
-    const BackArgs C{Nc, Csr{nullptr, nullptr, nullptr}, nullptr, nullptr, nullptr, scratch + b.dzc[1],
-                     params_bf16 + layer_at(0, kW1), acts + a.hc[0], scratch + b.dzc[0]};
-    hipLaunchKernelGGL(back_kernel, dim3(blocks_for(Nc)), dim3(256), 0, s, C);
   }
   Grads G{};
   G.rows = b.rows;
