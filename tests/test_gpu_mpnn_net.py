@@ -81,6 +81,10 @@ def single_kernels(net, G, dxhat):
 
 
 def instances(case):
+    if case[0] == "n":  # variables around the line where blocks share rows; degrees around 16 entries in flight
+        return [synth.random_ksat(int(case[1:]), 6 * int(case[1:]), 3, 9)]
+    if case == "longer":  # fewer constraints than variables: the constraints' rows are shared, some above 16 entries
+        return [synth.mixed_small(n=400, seed=6, kmax=40, count=333)]
     if case == "one":
         return [synth.random_ksat(3, 1, 3, 1)]
     if case == "tiles":  # 63 variables, 65 constraints
@@ -92,7 +96,7 @@ def instances(case):
     return [synth.c5_train(i) for i in range(3)] + [synth.c2_mixed(7, 300, 900, 90, 30)]
 
 
-@pytest.mark.parametrize("case", ["one", "tiles", "isolated", "types", "several"])
+@pytest.mark.parametrize("case", ["one", "tiles", "isolated", "types", "several", "n16383", "n16384", "n16385", "longer"])
 def test_network_equals_single_kernels(case):
     log(f"case {case}")
     G = learned.GraphBatch(instances(case), "cuda")
