@@ -1947,8 +1947,8 @@ __global__ void __launch_bounds__(1024) extract_bits_kernel(ProblemDev P, const 
       for (int j = 0; j < 9; ++j) pl[j] = 0u;
       int32_t code[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u)  // past the block: 0, not used
-        code[u] = __builtin_amdgcn_raw_buffer_load_b32(rs, (unsigned)cl * 4u, u * count_s * 4, 0);
+      for (int u = 0; u < 8; ++u)  // slots past the bucket's last repeat it, not used
+        code[u] = __builtin_amdgcn_raw_buffer_load_b32(rs, (unsigned)cl * 4u, min(u, kmax - 1) * count_s * 4, 0);
       for (int i = 0; i < kmax; i += 8) {
         uint32_t x[8];
 #pragma unroll
