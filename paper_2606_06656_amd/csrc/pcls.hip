@@ -2660,14 +2660,14 @@ int32_t pcls_state_from_rows(const pcls_problem* p, int32_t R, const float* d_ro
   int32_t st = check_bound(p);
   if (st != PCLS_OK) return st;
   if (R < 0) return set_error(PCLS_E_INVALID, "R must be >= 0");
-  if (R == 0) return PCLS_OK;
-  if (!d_rows || !d_x) return set_error(PCLS_E_INVALID, "d_rows and d_x must not be NULL");
+  if (R > 0 && (!d_rows || !d_x)) return set_error(PCLS_E_INVALID, "d_rows and d_x must not be NULL");
   const int R_pad = round_up64(R);
   hipStream_t s = (hipStream_t)stream;
   if (d_outside) {
     hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, s, d_outside, 0, 1);
     PCLS_HIP(hipGetLastError(), "fill launch");
   }
+  if (R == 0) return PCLS_OK;
   hipLaunchKernelGGL(state_rows_kernel, dim3(R_pad / 64, (p->n + 63) / 64), dim3(256), 0, s, d_rows, p->n, R, R_pad, d_x,
                      d_outside);
   PCLS_HIP(hipGetLastError(), "state_rows launch");
