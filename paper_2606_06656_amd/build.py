@@ -43,8 +43,9 @@ def objects():
     for maxb in ("kMaxbAll", "kMaxbMid", "kMaxbShort"):
         for bits, acc in ((32, "unsigned int"), (64, "unsigned long long")):
             # PCLS_VARIANT_LT: log2 of the restarts per tile, -1 any; -2 the batched
-            # engine, -3 the statistics, -4 codes in LDS
-            kinds = [-1, 0, -2] + ([-3] if bits == 32 else []) + ([1, 2, -4] if maxb == "kMaxbShort" else [])
+            # engine, -3 the statistics, -4 codes in LDS, -5 the same problems without
+            # (-6 in the batched engine)
+            kinds = [-1, 0, -2] + ([-3] if bits == 32 else []) + ([1, 2, -4, -5, -6] if maxb == "kMaxbShort" else [])
             for lt in kinds:
                 out.append((f"pcls_{maxb}_{bits}_{lt}.o", "pcls.hip",
                             [f"-DPCLS_VARIANT_MAXB={maxb}", f"-DPCLS_VARIANT_ACC={acc}", f"-DPCLS_VARIANT_LT={lt}"]))

@@ -162,6 +162,7 @@ struct ProblemDev {
   const uint32_t* c_viol;        // per constraint: ClassRec::violated
   int32_t const_unsat;           // violated constraints among those of constant spectrum
   int32_t unit_weights;          // all weights 1.0
+  int32_t pair_terms;            // one restart a tile: one objective term a (constraint, restart) pair (set by the kernel, in a batch by the host)
   int32_t max_k;
   const int32_t* occ;            // per variable: occurrences in non-constant constraints
   const int32_t* perm;           // planned index -> caller's constraint index

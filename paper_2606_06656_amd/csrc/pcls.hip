@@ -13,6 +13,7 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 
 #include "plan.h"
 
@@ -1052,10 +1053,11 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
         fetch_pair<KIND, J, KMAX, (MAXB > kMaxbShort)>(P, S, b + u * per_wave + sub, lig, f.p[u]);
     }
   };
-  auto eval = [&](int base, const FetchedU<J, U>& cur) {
+  auto eval_terms = [&](int base, const FetchedU<J, U>& cur, auto pair_terms) {
     // A chunk (aligned, fixed pairs per lane, fixed order) sums its objective
     // terms in FP32 and adds one exact fixed-point term: the result does not
-    // depend on which wave claimed the chunk.
+    // depend on which wave claimed the chunk.  pair_terms: one
+    // such term a pair, as the launches with the codes in LDS add them.
     float fchunk = 0.f;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -1118,12 +1120,22 @@ __device__ __forceinline__ void run_segment(const ProblemDev& P, const Segment& 
           eval_pair(sk, fp);
         }
       }
+      if constexpr (decltype(pair_terms)::value) {
+        facc.own += fixed_term(fchunk);
+        fchunk = 0.f;
+      }
     }
-    facc.own += fixed_term(fchunk);
+    if constexpr (!decltype(pair_terms)::value) facc.own += fixed_term(fchunk);
   };
+  auto eval = [&](int base, const FetchedU<J, U>& cur) { eval_terms(base, cur, std::false_type{}); };
   constexpr bool kHeavy = KIND == KIND_DFT || KIND == KIND_THR || (KIND == KIND_PMF && KMAX > 16);
   if constexpr (CL)
     deal_chunks<FetchedU<J, U>>(S.c_count, per_wave, L, fetch, eval);
+  else if (!ST && U > 1 && logT == 0 && P.pair_terms)
+    // a loop of its own: a branch inside the other one cost it 6 to 10%
+    run_chunks<kHeavy, FetchedU<J, U>>(S.c_count, claim, fetch, [&](int base, const FetchedU<J, U>& cur) {
+      eval_terms(base, cur, std::bool_constant<(!ST && U > 1)>{});
+    });
   else
     run_chunks<kHeavy, FetchedU<J, U>>(S.c_count, claim, fetch, eval);
 }
@@ -1567,7 +1579,9 @@ __device__ __forceinline__ void resident_tile(const ProblemDev& P, const TileArg
 // atomics, two barriers, the objective's reduction.  Codes from LDS and chunks dealt
 // in turn take out the first two, and the last wave finishes the objective while
 // the first ones work: 3-SAT of 50 variables 2.0 -> 0.9 us a step.
-template <int MAXB, class AT, int LT, bool CL>
+// PT: ProblemDev::pair_terms known at compile time, so that the loop it does not take
+// is not there.
+template <int MAXB, class AT, int LT, bool CL, bool PT>
 __global__ void __launch_bounds__(1024) tile_kernel(ProblemDev P, TileArgs A) {
   extern __shared__ __attribute__((aligned(16))) unsigned long long lds_raw[];  // 16 B: vector LDS accesses
   // Workgroups go to the eight XCDs in turn.  Within each 256 of them, an XCD's 32
@@ -1576,6 +1590,7 @@ __global__ void __launch_bounds__(1024) tile_kernel(ProblemDev P, TileArgs A) {
   unsigned tile = blockIdx.x;
   if ((tile | 255u) < gridDim.x) tile = (tile & ~255u) | ((tile & 7u) << 5) | ((tile >> 3) & 31u);
   A.r0 = (int)tile << (LT >= 0 ? LT : A.logT);
+  P.pair_terms = PT;
   resident_tile<MAXB, AT, LT, CL>(P, A, lds_raw);
 }
 
@@ -1646,12 +1661,15 @@ __device__ __forceinline__ ProblemDev load_problem(kptr<BatchInst> bi) {
   P.row_ptr = bi->P.row_ptr;
   P.lit = bi->P.lit;
   P.unit_weights = bi->P.unit_weights;
+  P.pair_terms = bi->P.pair_terms;
   P.max_k = bi->P.max_k;
   P.occ = bi->P.occ;
   return P;
 }
 
-template <int MAXB, class AT>
+// PT: some tile holds one restart of a problem with ProblemDev::pair_terms (both loops
+// in one kernel cost the uneven batch of 256 1.5%).
+template <int MAXB, class AT, bool PT>
 __global__ void __launch_bounds__(1024) batch_kernel(const BatchInst* __restrict__ insts,
                                                      const BatchItem* __restrict__ items, int n_items,
                                                      unsigned int* __restrict__ counter, float lr, int n_steps,
@@ -1667,7 +1685,7 @@ __global__ void __launch_bounds__(1024) batch_kernel(const BatchInst* __restrict
     if (it >= n_items) break;  // every workgroup reaches this once the list is drained
     kptr<BatchItem> W = kconst(items) + it;
     kptr<BatchInst> B = kconst(insts) + W->inst;
-    const ProblemDev P = load_problem(B);
+    ProblemDev P = load_problem(B);
     TileArgs A;
     A.X = B->X;
     A.R = B->R;
@@ -1686,6 +1704,7 @@ __global__ void __launch_bounds__(1024) batch_kernel(const BatchInst* __restrict
     A.fixed = nullptr;
     A.tol = 0.f;
     A.iters = nullptr;
+    if constexpr (!PT) P.pair_terms = 0;
     // tiles of two, four and eight restarts have code of their own (see tile_kernel)
     if (MAXB <= kMaxbShort && A.logT == 1)
       resident_tile<MAXB, AT, MAXB <= kMaxbShort ? 1 : -1>(P, A, lds_raw);
@@ -1702,14 +1721,19 @@ __global__ void __launch_bounds__(1024) batch_kernel(const BatchInst* __restrict
 #ifdef PCLS_VARIANT_MAXB
 
 #if PCLS_VARIANT_LT == -2
-template __global__ void batch_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC>(const BatchInst*, const BatchItem*, int,
-                                                                           unsigned int*, float, int, int);
+template __global__ void batch_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC, false>(const BatchInst*, const BatchItem*, int,
+                                                                                  unsigned int*, float, int, int);
+#elif PCLS_VARIANT_LT == -6
+template __global__ void batch_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC, true>(const BatchInst*, const BatchItem*, int,
+                                                                                 unsigned int*, float, int, int);
 #elif PCLS_VARIANT_LT == -3
 template __global__ void stats_kernel<PCLS_VARIANT_MAXB>(ProblemDev, const float*, int, int, int, StatsOut);
 #elif PCLS_VARIANT_LT == -4
-template __global__ void tile_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC, 0, true>(ProblemDev, TileArgs);
+template __global__ void tile_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC, 0, true, true>(ProblemDev, TileArgs);
+#elif PCLS_VARIANT_LT == -5
+template __global__ void tile_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC, 0, false, true>(ProblemDev, TileArgs);
 #else
-template __global__ void tile_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC, PCLS_VARIANT_LT, false>(ProblemDev, TileArgs);
+template __global__ void tile_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC, PCLS_VARIANT_LT, false, false>(ProblemDev, TileArgs);
 #endif
 
 }  // namespace engine
@@ -1717,23 +1741,27 @@ template __global__ void tile_kernel<PCLS_VARIANT_MAXB, PCLS_VARIANT_ACC, PCLS_V
 
 #else
 
-#define PCLS_EXTERN_TILE(MAXB, LT, CL)                                                                      \
-  extern template __global__ void tile_kernel<MAXB, unsigned int, LT, CL>(ProblemDev, TileArgs);            \
-  extern template __global__ void tile_kernel<MAXB, unsigned long long, LT, CL>(ProblemDev, TileArgs);
+#define PCLS_EXTERN_TILE(MAXB, LT, CL, PT)                                                                  \
+  extern template __global__ void tile_kernel<MAXB, unsigned int, LT, CL, PT>(ProblemDev, TileArgs);        \
+  extern template __global__ void tile_kernel<MAXB, unsigned long long, LT, CL, PT>(ProblemDev, TileArgs);
+#define PCLS_EXTERN_BATCH(MAXB, PT)                                                                                    \
+  extern template __global__ void batch_kernel<MAXB, unsigned int, PT>(const BatchInst*, const BatchItem*, int,        \
+                                                                       unsigned int*, float, int, int);                \
+  extern template __global__ void batch_kernel<MAXB, unsigned long long, PT>(const BatchInst*, const BatchItem*, int,  \
+                                                                             unsigned int*, float, int, int);
 #define PCLS_EXTERN_VARIANT(MAXB)                                                                                  \
-  PCLS_EXTERN_TILE(MAXB, -1, false)                                                                                \
-  PCLS_EXTERN_TILE(MAXB, 0, false)                                                                                 \
-  extern template __global__ void batch_kernel<MAXB, unsigned int>(const BatchInst*, const BatchItem*, int,        \
-                                                                   unsigned int*, float, int, int);                \
-  extern template __global__ void batch_kernel<MAXB, unsigned long long>(const BatchInst*, const BatchItem*, int,  \
-                                                                         unsigned int*, float, int, int);          \
+  PCLS_EXTERN_TILE(MAXB, -1, false, false)                                                                         \
+  PCLS_EXTERN_TILE(MAXB, 0, false, false)                                                                          \
+  PCLS_EXTERN_BATCH(MAXB, false)                                                                                   \
   extern template __global__ void stats_kernel<MAXB>(ProblemDev, const float*, int, int, int, StatsOut);
 PCLS_EXTERN_VARIANT(kMaxbShort)
 PCLS_EXTERN_VARIANT(kMaxbMid)
 PCLS_EXTERN_VARIANT(kMaxbAll)
-PCLS_EXTERN_TILE(kMaxbShort, 1, false)
-PCLS_EXTERN_TILE(kMaxbShort, 2, false)
-PCLS_EXTERN_TILE(kMaxbShort, 0, true)
+PCLS_EXTERN_TILE(kMaxbShort, 1, false, false)
+PCLS_EXTERN_TILE(kMaxbShort, 2, false, false)
+PCLS_EXTERN_TILE(kMaxbShort, 0, false, true)
+PCLS_EXTERN_TILE(kMaxbShort, 0, true, true)
+PCLS_EXTERN_BATCH(kMaxbShort, true)
 
 }  // namespace engine
 }  // namespace pcls
@@ -2107,21 +2135,25 @@ hipError_t check_no_static_lds(const void* f) {
 
 // The kernel of a launch: restarts per tile 2^lt where a variant is compiled for it.
 using TileKernel = void (*)(ProblemDev, TileArgs);
+// Variants of one restart a tile for problems whose codes fit LDS (codes_fit): with
+// the codes in LDS, and without (launches of few steps, evaluations).
+enum class Codes { none, fit, in_lds };
 template <int MAXB, class AT>
-TileKernel tile_variant_of(int lt) {
+TileKernel tile_variant_of(int lt, Codes codes) {
   if constexpr (MAXB <= kMaxbShort) {
-    if (lt == 1) return tile_kernel<MAXB, AT, 1, false>;
-    if (lt == 2) return tile_kernel<MAXB, AT, 2, false>;
+    if (lt == 0 && codes == Codes::in_lds) return tile_kernel<MAXB, AT, 0, true, true>;
+    if (lt == 0 && codes == Codes::fit) return tile_kernel<MAXB, AT, 0, false, true>;
+    if (lt == 1) return tile_kernel<MAXB, AT, 1, false, false>;
+    if (lt == 2) return tile_kernel<MAXB, AT, 2, false, false>;
   }
-  return lt == 0 ? tile_kernel<MAXB, AT, 0, false> : tile_kernel<MAXB, AT, -1, false>;
+  return lt == 0 ? tile_kernel<MAXB, AT, 0, false, false> : tile_kernel<MAXB, AT, -1, false, false>;
 }
-TileKernel tile_variant(int max_bucket, bool acc64, int lt, bool small) {
-  if (small) return acc64 ? tile_kernel<kMaxbShort, unsigned long long, 0, true> : tile_kernel<kMaxbShort, unsigned int, 0, true>;
+TileKernel tile_variant(int max_bucket, bool acc64, int lt, Codes codes) {
   if (max_bucket <= kMaxbShort)
-    return acc64 ? tile_variant_of<kMaxbShort, unsigned long long>(lt) : tile_variant_of<kMaxbShort, unsigned int>(lt);
+    return acc64 ? tile_variant_of<kMaxbShort, unsigned long long>(lt, codes) : tile_variant_of<kMaxbShort, unsigned int>(lt, codes);
   if (max_bucket <= kMaxbMid)
-    return acc64 ? tile_variant_of<kMaxbMid, unsigned long long>(lt) : tile_variant_of<kMaxbMid, unsigned int>(lt);
-  return acc64 ? tile_variant_of<kMaxbAll, unsigned long long>(lt) : tile_variant_of<kMaxbAll, unsigned int>(lt);
+    return acc64 ? tile_variant_of<kMaxbMid, unsigned long long>(lt, codes) : tile_variant_of<kMaxbMid, unsigned int>(lt, codes);
+  return acc64 ? tile_variant_of<kMaxbAll, unsigned long long>(lt, codes) : tile_variant_of<kMaxbAll, unsigned int>(lt, codes);
 }
 
 int32_t device_limits(DeviceLimits& out) {
@@ -2143,7 +2175,8 @@ int32_t device_limits(DeviceLimits& out) {
     for (int maxb : {kMaxbShort, kMaxbMid, kMaxbAll})
       for (int lt : {-1, 0, 1, 2})
         for (bool acc64 : {false, true})
-          for (bool small : {false, true}) variants.push_back((const void*)tile_variant(maxb, acc64, lt, small));
+          for (Codes codes : {Codes::none, Codes::fit, Codes::in_lds})
+            variants.push_back((const void*)tile_variant(maxb, acc64, lt, codes));
     for (const void* f : variants) {
       PCLS_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, d.lds_max), "hipFuncSetAttribute");
       PCLS_HIP(check_no_static_lds(f), "kernel attributes");
@@ -2172,7 +2205,7 @@ struct Launch {
   int block;
   size_t lds;
   bool acc64;
-  bool small;  // codes in LDS (tile_kernel's CL)
+  Codes codes;
 };
 
 // Restarts per workgroup: largest power of two whose state fits in LDS, at
@@ -2200,6 +2233,18 @@ bool auto_acc64(const pcls_problem* p, size_t cap) {
 constexpr int kSmallSteps = 8;
 size_t codes_lds_bytes(const pcls_problem* p) {
   return 16 + 4 * ((p->litT.size() + 3) / 4 * 4 + (size_t)p->m * (p->unit_weights ? 1 : 2)) + ((size_t)p->n + 3) / 4 * 4;
+}
+
+// Whether launches of the problem with one restart a tile may keep the codes in LDS:
+// such a launch has one pair a chunk, where the others sum up to four pairs in FP32
+// before an exact objective term.  All launches of such a problem then add a term a
+// pair (ProblemDev::pair_terms), so that its objectives do not depend on the number
+// of steps.  The other problems keep the sums: a term a pair costs them 4 to 6% of
+// a step (3-SAT of 3000 variables 4.88 -> 5.17 us, of 15000 at 1024 restarts 67.1 ->
+// 71.3), launches of 7 steps of 3-SAT of 2000 variables 34.6 -> 36.1 us.
+bool codes_fit(const pcls_problem* p, size_t cap) {
+  return p->max_bucket <= kMaxbShort &&
+         tile_lds_bytes(state_rows(p), 1, auto_acc64(p, cap) ? 8 : 4) + codes_lds_bytes(p) <= cap;
 }
 
 // steps: of the launch; 0 for an evaluation
@@ -2235,16 +2280,16 @@ int32_t choose_launch(const pcls_problem* p, int R, int steps, Launch& L) {
     return set_error(PCLS_E_UNSUPPORTED,
                      "state of %d variables x %d restarts needs %zu bytes of LDS (device limit %d)", p->n, T, lds,
                      lim.lds_max);
-  const size_t lds_small = lds + codes_lds_bytes(p);
-  L.small = T == 1 && steps >= kSmallSteps && p->max_bucket <= kMaxbShort && lds_small <= cap;
+  L.codes = T > 1 || !codes_fit(p, cap) ? Codes::none : (steps >= kSmallSteps ? Codes::in_lds : Codes::fit);
+  const bool in_lds = L.codes == Codes::in_lds;
   int block = p->block_threads;
-  if (block <= 0) block = (L.small || lds > cap / 2 || R_pad / T <= lim.n_cu) ? 1024 : 512;
+  if (block <= 0) block = (in_lds || lds > cap / 2 || R_pad / T <= lim.n_cu) ? 1024 : 512;
   if (block != 256 && block != 512 && block != 1024)
     return set_error(PCLS_E_INVALID, "block_threads %d must be 256, 512 or 1024", block);
   L.logT = 0;
   while ((1 << L.logT) < T) ++L.logT;
   L.block = block;
-  L.lds = L.small ? lds_small : lds;
+  L.lds = in_lds ? lds + codes_lds_bytes(p) : lds;
   L.acc64 = acc64;
   return PCLS_OK;
 }
@@ -2281,7 +2326,7 @@ int32_t launch_tile(const pcls_problem* p, int R, float* d_x, float lr, int n_st
   A.fixed = opt ? opt->d_fixed : nullptr;
   A.tol = opt ? opt->tol : 0.f;
   A.iters = opt ? opt->d_iters : nullptr;
-  const TileKernel kern = tile_variant(p->max_bucket, L.acc64, L.logT, L.small);
+  const TileKernel kern = tile_variant(p->max_bucket, L.acc64, L.logT, L.codes);
   hipLaunchKernelGGL(kern, dim3(tiles), dim3(L.block), L.lds, stream, p->dev, A);
   PCLS_HIP(hipGetLastError(), "tile_kernel launch");
   return PCLS_OK;
@@ -2296,6 +2341,7 @@ struct BatchState {
   pcls_batch_config cfg{};
   bool acc64 = true;
   int maxb = 0;
+  bool pair_terms = false;  // some tile needs batch_kernel's PT
   int n_items = 0;
   size_t lds = 0;   // dynamic LDS of the persistent launch
   int grid = 0;
@@ -2357,6 +2403,7 @@ int32_t batch_configure(BatchState& b, const pcls_batch_config& cfg_in, hipStrea
   }
   const int ab = acc64 ? 8 : 4;
   b.maxb = 0;
+  b.pair_terms = false;
   b.items.clear();
   b.inst.resize(b.probs.size());
   size_t lds = 0;
@@ -2384,6 +2431,8 @@ int32_t batch_configure(BatchState& b, const pcls_batch_config& cfg_in, hipStrea
       work.push_back({(double)p->L * T + (double)p->n * T, BatchItem{(int)i, r0, logT, 0}});
     BatchInst& I = b.inst[i];
     I.P = p->dev;
+    I.P.pair_terms = codes_fit(p, (size_t)lim.lds_max);
+    if (T == 1 && I.P.pair_terms) b.pair_terms = true;
     I.X = b.x[i];
     I.trace = b.trace[i];
     I.R = b.R[i];
@@ -2427,6 +2476,16 @@ int32_t batch_configure(BatchState& b, const pcls_batch_config& cfg_in, hipStrea
   return PCLS_OK;
 }
 
+using BatchKernel = void (*)(const BatchInst*, const BatchItem*, int, unsigned int*, float, int, int);
+template <class AT>
+BatchKernel batch_variant_of(int maxb, bool pair_terms) {
+  if (maxb <= kMaxbShort) return pair_terms ? batch_kernel<kMaxbShort, AT, true> : batch_kernel<kMaxbShort, AT, false>;
+  return maxb <= kMaxbMid ? batch_kernel<kMaxbMid, AT, false> : batch_kernel<kMaxbAll, AT, false>;
+}
+BatchKernel batch_variant(int maxb, bool acc64, bool pair_terms) {
+  return acc64 ? batch_variant_of<unsigned long long>(maxb, pair_terms) : batch_variant_of<unsigned int>(maxb, pair_terms);
+}
+
 int32_t batch_launch(BatchState& b, float lr, int n_steps, hipStream_t stream) {
   uint8_t* base = (uint8_t*)b.d_ws;
   const BatchInst* insts = (const BatchInst*)(base + b.off_inst);
@@ -2436,17 +2495,8 @@ int32_t batch_launch(BatchState& b, float lr, int n_steps, hipStream_t stream) {
   hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, stream, counter, 0u, 1);
   PCLS_HIP(hipGetLastError(), "fill launch");
   const dim3 grid(b.grid), block(b.cfg.block_threads);
-  if (b.acc64) {
-    auto k = b.maxb <= kMaxbShort ? batch_kernel<kMaxbShort, unsigned long long>
-                         : (b.maxb <= kMaxbMid ? batch_kernel<kMaxbMid, unsigned long long> : batch_kernel<kMaxbAll, unsigned long long>);
-    hipLaunchKernelGGL(k, grid, block, b.lds + 256, stream, insts, items, b.n_items, counter, lr, n_steps,
-                       (int)b.lds);
-  } else {
-    auto k = b.maxb <= kMaxbShort ? batch_kernel<kMaxbShort, unsigned int>
-                         : (b.maxb <= kMaxbMid ? batch_kernel<kMaxbMid, unsigned int> : batch_kernel<kMaxbAll, unsigned int>);
-    hipLaunchKernelGGL(k, grid, block, b.lds + 256, stream, insts, items, b.n_items, counter, lr, n_steps,
-                       (int)b.lds);
-  }
+  hipLaunchKernelGGL(batch_variant(b.maxb, b.acc64, b.pair_terms), grid, block, b.lds + 256, stream, insts, items, b.n_items,
+                     counter, lr, n_steps, (int)b.lds);
   PCLS_HIP(hipGetLastError(), "batch_kernel launch");
   return PCLS_OK;
 }
@@ -2462,14 +2512,14 @@ int32_t batch_attrs() {
   if (st != PCLS_OK) return st;
   std::lock_guard<std::mutex> lk(g_batch_attr_mu);
   if (dev >= 0 && dev < 64 && !g_batch_attr_set[dev]) {
-    const void* fs[] = {(const void*)batch_kernel<kMaxbShort, unsigned long long>, (const void*)batch_kernel<kMaxbMid, unsigned long long>,
-                        (const void*)batch_kernel<kMaxbAll, unsigned long long>, (const void*)batch_kernel<kMaxbShort, unsigned int>,
-                        (const void*)batch_kernel<kMaxbMid, unsigned int>, (const void*)batch_kernel<kMaxbAll, unsigned int>};
-    for (const void* f : fs) {
-      PCLS_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim.lds_max),
-               "hipFuncSetAttribute");
-      PCLS_HIP(check_no_static_lds(f), "batch kernel attributes");
-    }
+    for (int maxb : {kMaxbShort, kMaxbMid, kMaxbAll})
+      for (bool acc64 : {false, true})
+        for (bool pair_terms : {false, true}) {
+          const void* f = (const void*)batch_variant(maxb, acc64, pair_terms);
+          PCLS_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim.lds_max),
+                   "hipFuncSetAttribute");
+          PCLS_HIP(check_no_static_lds(f), "batch kernel attributes");
+        }
     g_batch_attr_set[dev] = true;
   }
   return PCLS_OK;
