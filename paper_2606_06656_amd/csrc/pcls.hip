@@ -2226,10 +2226,12 @@ bool auto_acc64(const pcls_problem* p, size_t cap) {
 }
 
 // Codes in LDS (tile_kernel's CL): one restart a tile, the codes fit next to the
-// state, and enough steps to pay for copying them.  Measured against the same
-// variant without (us a step): 3-SAT of 50, 200, 1000, 2000 variables 0.91, 1.18,
-// 2.18, 3.38 against 1.67, 2.07, 2.83, 3.84; mixed instance of 2000 variables 3.98
-// against 4.77; copying costs up to about 3 us.
+// state, enough steps to pay for copying them, and no fewer tiles on a CU for it.
+// Measured against the same launch without (us a step, 3-SAT of 50, 200, 1000, 2000
+// variables): 64 restarts 0.95, 1.20, 2.28, 3.69 against 1.69, 2.08, 2.81, 3.85;
+// copying costs up to about 3 us.  320 restarts (two tiles of 512 threads a CU)
+// 1.06, 1.48, 3.57 against 1.84, 2.26, 3.66; at 2000 variables only one tile fits with
+// its codes: 7.36 with 1024 threads and 9.39 with 512, against 6.13 without.
 constexpr int kSmallSteps = 8;
 size_t codes_lds_bytes(const pcls_problem* p) {
   return 16 + 4 * ((p->litT.size() + 3) / 4 * 4 + (size_t)p->m * (p->unit_weights ? 1 : 2)) + ((size_t)p->n + 3) / 4 * 4;
@@ -2280,16 +2282,21 @@ int32_t choose_launch(const pcls_problem* p, int R, int steps, Launch& L) {
     return set_error(PCLS_E_UNSUPPORTED,
                      "state of %d variables x %d restarts needs %zu bytes of LDS (device limit %d)", p->n, T, lds,
                      lim.lds_max);
-  L.codes = T > 1 || !codes_fit(p, cap) ? Codes::none : (steps >= kSmallSteps ? Codes::in_lds : Codes::fit);
-  const bool in_lds = L.codes == Codes::in_lds;
   int block = p->block_threads;
-  if (block <= 0) block = (in_lds || lds > cap / 2 || R_pad / T <= lim.n_cu) ? 1024 : 512;
+  if (block <= 0) block = (lds > cap / 2 || R_pad / T <= lim.n_cu) ? 1024 : 512;
   if (block != 256 && block != 512 && block != 1024)
     return set_error(PCLS_E_INVALID, "block_threads %d must be 256, 512 or 1024", block);
+  // tiles side by side on a CU: by LDS and 16 waves, no more than there are for it
+  auto resident = [&](size_t bytes) {
+    return std::min({(int)(cap / bytes), 1024 / block, (R + T * lim.n_cu - 1) / (T * lim.n_cu)});
+  };
+  const size_t lds_codes = lds + codes_lds_bytes(p);
+  L.codes = T == 1 && codes_fit(p, cap) ? Codes::fit : Codes::none;
+  if (L.codes == Codes::fit && steps >= kSmallSteps && resident(lds_codes) >= resident(lds)) L.codes = Codes::in_lds;
   L.logT = 0;
   while ((1 << L.logT) < T) ++L.logT;
   L.block = block;
-  L.lds = in_lds ? lds + codes_lds_bytes(p) : lds;
+  L.lds = L.codes == Codes::in_lds ? lds_codes : lds;
   L.acc64 = acc64;
   return PCLS_OK;
 }
