@@ -8,7 +8,7 @@ with the batched engine's configuration (threads per workgroup and LDS budget,
 searched by the library's pcls_batch_autotune).  Both time short launches on
 scratch states, never on the caller's, and cache the winner in a JSON file
 keyed by a signature of the workload (sizes, the histogram of constraint
-classes, the restart count and the device).
+classes, the restart count, the device and the kernels' revision).
 
 For one bucket table the gradients are exact fixed-point sums, so the tile and
 block sizes change only the time, not the iterates; the table changes how long
@@ -27,6 +27,10 @@ import numpy as np
 from . import pcls
 
 TABLES = (0, 1)  # pcls_plan_options.bucket_table
+# Steps of a probe of problems with constraints up to 8 literals, at least: launches of
+# 8 steps or more may run another kernel there (codes on chip), and a launch's fixed
+# cost (some 8 us, copying the codes among it) is no step's.
+SHORT_PROBE_STEPS = 32
 
 
 def _device_name(device) -> str:
@@ -36,7 +40,7 @@ def _device_name(device) -> str:
 
 def workload_signature(instances, restarts, device) -> str:
     """Sizes, class histogram ((type, length, parameter) counts), weights kind,
-    restart counts and device of a workload."""
+    restart counts and device of a workload, and the kernels' revision."""
     h = hashlib.sha256()
     for inst, R in zip(instances, restarts):
         k = np.diff(inst.row_ptr)
@@ -44,7 +48,7 @@ def workload_signature(instances, restarts, device) -> str:
         w = "unit" if inst.weight is None or bool(np.all(inst.weight == 1)) else "weighted"
         h.update(f"{inst.n},{inst.m},{inst.L},{R},{w};".encode())
         h.update(repr(sorted(hist.items())).encode())
-    h.update(_device_name(device).encode())
+    h.update(f"{_device_name(device)},{pcls.KERNEL_REVISION}".encode())
     return h.hexdigest()[:24]
 
 
@@ -81,11 +85,14 @@ def tune_problem(inst, R: int, lr: float = 0.1, probe_steps: int = 3, tables=TAB
                  cache_path: str | None = None, device="cuda:0"):
     """Fastest (bucket table, restarts per workgroup, threads per workgroup) for
     R restarts of inst: the automatic tile, half and twice it, under each table
-    and block size."""
+    and block size.  Probes are launches of probe_steps steps, of SHORT_PROBE_STEPS
+    at least where every constraint has at most 8 literals."""
     key = "problem:" + workload_signature([inst], [R], device)
     cache = _load_cache(cache_path)
     if key in cache:
         return dict(cache[key], cached=True)
+    if int(np.diff(inst.row_ptr).max(initial=0)) <= 8:
+        probe_steps = max(probe_steps, SHORT_PROBE_STEPS)
     cands = []
     for table in tables:
         prob = pcls.Problem.from_instance(inst, device=device, bucket_table=table)

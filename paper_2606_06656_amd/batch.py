@@ -135,7 +135,7 @@ class Batch:
         pcls.check(_lib().pcls_batch_replay(self.handle, pcls._stream()))
 
     def signature(self) -> str:
-        h = hashlib.sha256()
+        h = hashlib.sha256(pcls.KERNEL_REVISION.encode())
         for p, r in zip(self.problems, self.restarts):
             info = p.info()
             h.update(f"{info.n_vars},{info.n_cons},{info.n_lits},{info.max_len},{r};".encode())

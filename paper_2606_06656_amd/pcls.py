@@ -20,6 +20,9 @@ PCLS_OK, PCLS_E_INVALID, PCLS_E_UNSUPPORTED, PCLS_E_DUPVAR, PCLS_E_WORKSPACE, PC
 STATUS_NAMES = {0: "PCLS_OK", 1: "PCLS_E_INVALID", 2: "PCLS_E_UNSUPPORTED", 3: "PCLS_E_DUPVAR",
                 4: "PCLS_E_WORKSPACE", 5: "PCLS_E_HIP"}
 
+# of the engine's kernels and launch rules: launches tuned for another one are tuned anew
+KERNEL_REVISION = "2"
+
 # exported entry points (checked by the CPU test suite against include/pcls.h)
 EXPORTS = ["pcls_plan", "pcls_plan_ex", "pcls_problem_info", "pcls_upload", "pcls_init_restarts",
            "pcls_init_restarts_masked",
