@@ -35,7 +35,7 @@ enum Kind : int32_t { KIND_PROD1 = 0, KIND_PROD2 = 1, KIND_DFT = 2, KIND_PMF = 3
 constexpr int kNumKinds = 5;
 constexpr int kPmfWindow = 4;  // counts kept by the PMF kind, one lane per pair (k <= 8)
 constexpr int kPmfMaxK = 8;    // longest constraint of the one-lane PMF kind
-constexpr int kThrMaxK = 64;       // longest bucket of the THR kind
+constexpr int kThrMaxK = 64;   // longest bucket of the THR kind
 constexpr int kPmfGroupMaxK = 48;  // longest constraint of the lane-group PMF kind (window <= bucket / 2)
 
 // Length buckets of the segment kernels: literals per constraint padded to KMAX,
@@ -47,7 +47,17 @@ constexpr int kMaxbShort = 7;                // k <= 8
 constexpr int kMaxbMid = 11;                 // k <= 32
 constexpr int kMaxbAll = kNumBuckets - 1;    // k <= 256
 constexpr int kMaxK = 256;
-constexpr int kMaxSegments = 4 * kNumBuckets;  // (kind, bucket) pairs of the non-constant kinds
+// (kind, bucket) pairs of the non-constant kinds: the products and DFT have every
+// bucket, PMF and THR these (the kernels' cases; LDS holds one counter a segment)
+constexpr bool runs_pmf(int kmax) { return kmax <= kPmfMaxK || (kmax > 16 && kmax <= kPmfGroupMaxK); }
+constexpr bool runs_thr(int kmax) { return kmax > kPmfMaxK && kmax <= kThrMaxK; }
+constexpr int count_segments() {
+  int count = 0;
+  for (int kmax : kBucketKmax) count += 3 + runs_pmf(kmax) + runs_thr(kmax);
+  return count;
+}
+constexpr int kMaxSegments = 72;
+static_assert(count_segments() <= kMaxSegments, "a plan's segments need a counter each");
 // Pad rows: problems with constraints longer than 8 literals get kPadRows extra
 // rows in the on-chip state, held at x = +1 and never stepped.  A slot past a
 // constraint's end (length buckets above 8) codes one of these rows, with the

@@ -236,7 +236,7 @@ static void classify(const std::vector<int>& sp, bool force_generic, int table, 
 // counts, and room for W - w certain pad slots.  Sets the window, h and d_0.
 static bool aligned_threshold(const std::vector<int>& sp, int table, ClassRec& C, float* h, float* d0) {
   const int k = (int)sp.size() - 1, kb = kBucketKmax[bucket_of(k, table)];
-  if (k <= kPmfMaxK || kb > kThrMaxK || (C.kind != KIND_PMF && C.kind != KIND_DFT)) return false;
+  if (!runs_thr(kb) || (C.kind != KIND_PMF && C.kind != KIND_DFT)) return false;
   std::vector<float> d((size_t)k + 1);
   const int w = pmf_window(sp, d.data(), h, k + 1);
   if (2 * w > kb || kb / 2 - w > kb - k) return false;
@@ -455,7 +455,7 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
         C.c0 = (float)(h > 0.f ? sp[(size_t)k] : sp[0]);
       }
       // windows of up to 16 literals: one lane without nodes (the DFT kind) is faster
-      if (C.kind == KIND_PMF && k > kPmfMaxK && kBucketKmax[bucket_of(k, P->bucket_table)] <= 16) C.kind = KIND_DFT;
+      if (C.kind == KIND_PMF && !runs_pmf(kBucketKmax[bucket_of(k, P->bucket_table)])) C.kind = KIND_DFT;
       if (C.kind == KIND_DFT) {
         const int kmax = kBucketKmax[bucket_of(k, P->bucket_table)];
         dft_class(sp, kmax, roots(kmax), C, P->nodes);
