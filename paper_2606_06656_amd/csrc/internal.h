@@ -32,7 +32,6 @@ namespace pcls {
 //           W - w.  All classes of a bucket then run the same code, and the sums over
 //           the window are running sums.  (Listed as PMF up to 48 literals, as DFT above.)
 enum Kind : int32_t { KIND_PROD1 = 0, KIND_PROD2 = 1, KIND_DFT = 2, KIND_PMF = 3, KIND_CONST = 4, KIND_THR = 5 };
-constexpr int kNumKinds = 5;
 constexpr int kPmfWindow = 4;  // counts kept by the PMF kind, one lane per pair (k <= 8)
 constexpr int kPmfMaxK = 8;    // longest constraint of the one-lane PMF kind
 constexpr int kThrMaxK = 64;   // longest bucket of the THR kind
@@ -118,7 +117,6 @@ struct Segment {
 struct ClassRec {
   int32_t kind;
   int32_t k;
-  int32_t n_nodes;   // DFT, PMF: entries of the node table
   int32_t node_off;  // DFT, PMF: offset into the node table (entries)
   int32_t window;    // PMF, THR: window w
   int32_t listed;    // kind it is counted under (pcls_info)

@@ -324,7 +324,6 @@ static void dft_class(const std::vector<int>& sp, int kmax, const Roots& w, Clas
   }
   C.node_off = (int32_t)nodes.size();
   put_floats(rec, nodes);
-  C.n_nodes = (int32_t)nodes.size() - C.node_off;
 }
 
 // The powers z_m^1..z_m^J of the nodes of a bucket (J literals a lane).
@@ -468,7 +467,6 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
         N.f[4] = h;
         C.c0 = (float)(h > 0.f ? sp[k] : sp[0]);
         C.node_off = (int32_t)P->nodes.size();
-        C.n_nodes = 1;
         P->nodes.push_back(N);
       } else if (C.kind == KIND_PMF) {
         // lane-group PMF: d_0..d_31, h, in five node records
@@ -479,7 +477,6 @@ int32_t build_plan(int32_t n, int32_t m, const int32_t* row_ptr, const int32_t* 
         rec[32] = h;
         C.c0 = (float)(h > 0.f ? sp[k] : sp[0]);
         C.node_off = (int32_t)P->nodes.size();
-        C.n_nodes = 5;
         for (int r = 0; r < 5; ++r) {
           NodeRec N;
           std::memcpy(&N, rec + 8 * r, sizeof N);
