@@ -214,15 +214,22 @@ __device__ __forceinline__ void gather4(const Csr& g, const float* In, int row0,
   }
 }
 
-// Few nodes of many entries: 16 rows a wave leave CUs idle, and a row's entries come
-// in latencies of four.  There the block's four waves gather for the same 16 rows,
-// one row a lane group with 16 entries in flight, and the first goes on with the
-// messages from LDS.  Taken up to about the blocks that the card holds at once, by
-// the side with fewer nodes, which has the longer rows (both sides have the same
-// entries).  Measured against 16 rows a wave: training step of 3200 variables of
-// degree 12.6 213 -> 165 us, predict with 16000 variables 149 -> 142 us; with the
-// 13440 constraints of 3 sharing as well the training step took 183 us.
-constexpr int kSharedRows = 16 * 1024;
+// Few nodes: 16 rows a wave leave CUs idle, and a row's entries come in latencies of
+// four.  There the block's four waves gather for the same 16 rows, one row a lane group
+// with 16 entries in flight, and the first goes on with the messages from LDS.
+// Measured for one side against 16 rows a wave (forward pass and training step, us;
+// n x k: n rows of about k entries):
+//   800 x 12.6    79 -> 52, 185 -> 133    8192 x 3    70 -> 59, 166 -> 143
+//   3200 x 12.6   96 -> 69, 218 -> 164    8000 x 5    83 -> 64, 187 -> 150
+//   10000 x 3     77 -> 75, 176 -> 185    12000 x 3   78 -> 82, 193 -> 206
+//   10000 x 6     93 -> 83, 222 -> 212    12000 x 9  116 -> 105, 298 -> 288
+//   16000 x 5     92 -> 93, 227 -> 237    16000 x 6   96 -> 94, 255 -> 257
+//   16000 x 12.6 157 -> 148, 451 -> 450   24000 x 12.6 188 -> 195, 592 -> 626
+// Up to kSharedRows, 512 blocks, two a CU (all that back_kernel's LDS lets a CU hold),
+// it is faster at any length; up to twice as many only for long rows.  The host does
+// not know the lengths: it takes variables with at least two constraints each, whose
+// rows are long where constraints are of three literals or more.
+constexpr int kSharedRows = 8192;
 
 // Messages of one row, 4 (lane / 16) + e of the 16; as gather4 otherwise
 template <bool kSplit>
@@ -340,7 +347,7 @@ struct RoundArgs {
   const float* wo;     // or NULL: xhat = tanh(H' . wo + bo)
   const float* bo;
   float* xhat;
-  bool shared;         // gather_shared
+  bool shared;         // gathered by the block together (gather1)
 };
 
 __global__ void __launch_bounds__(256) round_kernel(RoundArgs A) {
@@ -453,7 +460,7 @@ struct BackArgs {
   const uint16_t* Wself; // [64][64]
   const float* H;        // [N][64]
   float* dZ;             // [N][64]
-  bool shared;           // gather_shared
+  bool shared;           // gathered by the block together (gather1)
 };
 
 // blocks0 as in embed_kernel
@@ -679,9 +686,10 @@ __global__ void __launch_bounds__(256) wgrad_sum_kernel(Grads A, const float* __
 
 // ------------------------------------------------------------------- host
 int blocks_for(int N) { return N > 0 ? ((N + 63) / 64 < 1024 ? (N + 63) / 64 : 1024) : 0; }
-bool gather_shared(int N, int others) { return N <= kSharedRows && N <= others; }
+bool constraints_shared(int Nc) { return Nc <= kSharedRows; }
+bool variables_shared(int Nv, int Nc) { return Nv <= kSharedRows || (Nv <= 2 * kSharedRows && 2 * Nv <= Nc); }
 // blocks of a kernel that gathers for N rows
-int gather_blocks(int N, int others) { return gather_shared(N, others) ? (N + 15) / 16 : blocks_for(N); }
+int gather_blocks(int N, bool shared) { return shared ? (N + 15) / 16 : blocks_for(N); }
 
 // Activations kept by the forward pass (floats): H of the embedding and of each
 // round, variables then constraints, and the two 128-column products.
@@ -765,6 +773,7 @@ int32_t pcls_mpnn_forward(const pcls_mpnn_graph* g, const float* params, const u
     return fail(1, "forward: parameters, features and activations must be 16-byte aligned");
   hipStream_t s = (hipStream_t)stream;
   const int Nv = g->n_vars, Nc = g->n_cons;
+  const bool cons = constraints_shared(Nc), vars = variables_shared(Nv, Nc);
   const Acts a = acts_of((size_t)Nv, (size_t)Nc);
   if (Nv > 0 || Nc > 0) {
     const EmbedArgs V{g->feat_v,       Nv, params_bf16 + kEv, params + kev, acts + a.hv[0], params_bf16 + layer_at(0, kWpn),
@@ -777,15 +786,15 @@ int32_t pcls_mpnn_forward(const pcls_mpnn_graph* g, const float* params, const u
     if (Nc > 0) {
       const RoundArgs C{acts + a.hc[l], Nc, params_bf16 + layer_at(l, kW1), params + layer_at(l, kbc),
                         Csr{g->cptr, g->cidx, g->cw}, acts + a.pm, acts + a.hc[l + 1],
-                        params_bf16 + layer_at(l, kUpn), acts + a.qm, nullptr, nullptr, nullptr, gather_shared(Nc, Nv)};
-      hipLaunchKernelGGL(round_kernel, dim3(gather_blocks(Nc, Nv)), dim3(256), 0, s, C);
+                        params_bf16 + layer_at(l, kUpn), acts + a.qm, nullptr, nullptr, nullptr, cons};
+      hipLaunchKernelGGL(round_kernel, dim3(gather_blocks(Nc, cons)), dim3(256), 0, s, C);
     }
     if (Nv > 0) {
       const RoundArgs V{acts + a.hv[l], Nv, params_bf16 + layer_at(l, kW2), params + layer_at(l, kbv),
                         Csr{g->vptr, g->vidx, g->vw}, acts + a.qm, acts + a.hv[l + 1],
                         last ? nullptr : params_bf16 + layer_at(l + 1, kWpn), acts + a.pm,
-                        last ? params + kWo : nullptr, params + kBo, xhat, gather_shared(Nv, Nc)};
-      hipLaunchKernelGGL(round_kernel, dim3(gather_blocks(Nv, Nc)), dim3(256), 0, s, V);
+                        last ? params + kWo : nullptr, params + kBo, xhat, vars};
+      hipLaunchKernelGGL(round_kernel, dim3(gather_blocks(Nv, vars)), dim3(256), 0, s, V);
     }
   }
   return hip_check(hipGetLastError(), "forward launch");
@@ -800,6 +809,7 @@ int32_t pcls_mpnn_backward(const pcls_mpnn_graph* g, const float* params, const 
        (uintptr_t)g->feat_c) & 15u)
     return fail(1, "backward: parameters, features, activations and scratch must be 16-byte aligned");
   const int Nv = g->n_vars, Nc = g->n_cons;
+  const bool cons = constraints_shared(Nc), vars = variables_shared(Nv, Nc);
   const Acts a = acts_of((size_t)Nv, (size_t)Nc);
   const Back b = back_of(Nv, Nc);
   if (scratch_floats < b.total) return fail(4, "backward: scratch too small");
@@ -814,18 +824,18 @@ int32_t pcls_mpnn_backward(const pcls_mpnn_graph* g, const float* params, const 
       const BackArgs C{Nc, Csr{g->cptr, g->cidx, g->cw_t}, scratch + b.dzv[l + 1], params_bf16 + layer_at(l, kUpn),
                        scratch + b.dq[l], top ? nullptr : scratch + b.dzc[l + 2],
                        top ? nullptr : params_bf16 + layer_at(l + 1, kW1), acts + a.hc[l + 1], scratch + b.dzc[l + 1],
-                       gather_shared(Nc, Nv)};
-      hipLaunchKernelGGL(back_kernel, dim3(gather_blocks(Nc, Nv)), dim3(256), 0, s, C, gather_blocks(Nc, Nv), C);
+                       cons};
+      hipLaunchKernelGGL(back_kernel, dim3(gather_blocks(Nc, cons)), dim3(256), 0, s, C, gather_blocks(Nc, cons), C);
     }
     if (Nv > 0 || (l == 0 && Nc > 0)) {
       const BackArgs V{Nv, Csr{g->vptr, g->vidx, g->vw_t}, scratch + b.dzc[l + 1], params_bf16 + layer_at(l, kWpn),
                        scratch + b.dp[l], scratch + b.dzv[l + 1], params_bf16 + layer_at(l, kW2), acts + a.hv[l],
-                       scratch + b.dzv[l], gather_shared(Nv, Nc)};
+                       scratch + b.dzv[l], vars};
       // the constraint embedding's gradient needs no more than round 0's
       const BackArgs C{Nc, Csr{nullptr, nullptr, nullptr}, nullptr, nullptr, nullptr, scratch + b.dzc[1],
                        params_bf16 + layer_at(0, kW1), acts + a.hc[0], scratch + b.dzc[0], false};
       const int with = l == 0 ? blocks_for(Nc) : 0;
-      hipLaunchKernelGGL(back_kernel, dim3(gather_blocks(Nv, Nc) + with), dim3(256), 0, s, V, gather_blocks(Nv, Nc), C);
+      hipLaunchKernelGGL(back_kernel, dim3(gather_blocks(Nv, vars) + with), dim3(256), 0, s, V, gather_blocks(Nv, vars), C);
     }
   }
   Grads G{};
