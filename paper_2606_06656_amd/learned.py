@@ -338,7 +338,6 @@ class Params:
 class MPNN:
     def __init__(self, params: Params):
         self.P = params
-        self.scratch = Scratch(params.master.device)
 
     def forward(self, G: GraphBatch, keep=False):
         import torch
@@ -352,11 +351,13 @@ class MPNN:
 
     def backward(self, dxhat):
         """Gradients of every parameter (written, not accumulated) from dL/dxhat."""
+        import torch
         L, P = _lib(), self.P
         acts, xhat, G = self._cache
-        buf, nb = self.scratch.get(4 * L.pcls_mpnn_backward_floats(G.Nv, G.Nc))
+        # given back at once: 2.5 KB a node, which a network kept would hold between steps
+        buf = torch.empty(L.pcls_mpnn_backward_floats(G.Nv, G.Nc) + 4, dtype=torch.float32, device=G.device)
         _ck(L.pcls_mpnn_backward(ctypes.byref(G.c_graph()), _p(P.master), _p(P.bf16), _p(acts), _p(xhat), _p(dxhat),
-                                 _p(P.grad), _p(buf), nb // 4, _s()))
+                                 _p(P.grad), _p(buf), buf.numel(), _s()))
 
     def mse_loss_grad(self, xhat, y):
         """dL/dxhat for L = mean (xhat - y)^2; returns (dxhat, loss tensor)."""
