@@ -22,7 +22,8 @@
  *  - Gradients are accumulated in exact fixed point, so they (and hence the
  *    iterates) are bitwise reproducible and independent of the launch shape;
  *    objectives are FP32 sums over fixed work chunks added in exact fixed point,
- *    bitwise reproducible for a given launch shape.  The fixed-point scales are
+ *    bitwise reproducible for a given launch shape (restarts per workgroup),
+ *    however the steps are split into launches.  The fixed-point scales are
  *    chosen per problem (see pcls_info) so that no sum overflows.
  *  - All device pointers are caller-owned (hipMalloc'd or torch tensors).
  *    Every device operation is enqueued asynchronously on the given HIP
@@ -243,7 +244,9 @@ int32_t pcls_set_launch(pcls_problem* p, int32_t tile_restarts, int32_t block_th
  * device: restarts per workgroup, threads per workgroup, gradient accumulator
  * width (32 or 64), its fixed-point scale log2 (a gradient sum is exact in units
  * of 2^-S; each term is rounded to the nearest unit) and LDS bytes per
- * workgroup.  Any output pointer may be NULL.  Queries the device (no launch).
+ * workgroup (of a launch of 8 steps or more, which may hold a small problem's
+ * literal codes; shorter launches and evaluations then take less).  Any output
+ * pointer may be NULL.  Queries the device (no launch).
  */
 int32_t pcls_launch_info(const pcls_problem* p, int32_t R, int32_t* tile_restarts, int32_t* block_threads,
                          int32_t* accumulator_bits, int32_t* grad_scale_log2, size_t* lds_bytes);

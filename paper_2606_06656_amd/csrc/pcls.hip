@@ -2208,10 +2208,6 @@ struct Launch {
   Codes codes;
 };
 
-// Restarts per workgroup: largest power of two whose state fits in LDS, at
-// most 64 / G_max (a lane group must stay inside one wave), and small enough
-// to give every compute unit at least two tiles when R allows it.  The 64-bit
-// gradient accumulator is used whenever its tile fits, else the 32-bit one.
 // Automatic accumulator width.  A 32-bit accumulator whose quantum is at most
 // 2^-24 (the FP32 unit roundoff at 1) adds no more error per term than the FP32
 // arithmetic that produced the term, and halves the LDS atomic traffic and the
@@ -2249,7 +2245,9 @@ bool codes_fit(const pcls_problem* p, size_t cap) {
          tile_lds_bytes(state_rows(p), 1, auto_acc64(p, cap) ? 8 : 4) + codes_lds_bytes(p) <= cap;
 }
 
-// steps: of the launch; 0 for an evaluation
+// Restarts per workgroup: largest power of two whose state fits in LDS, at
+// most 64 / G_max (a lane group must stay inside one wave), and small enough
+// to give every compute unit a tile.  steps: of the launch; 0 for an evaluation.
 int32_t choose_launch(const pcls_problem* p, int R, int steps, Launch& L) {
   DeviceLimits lim;
   int32_t st = device_limits(lim);
