@@ -242,7 +242,8 @@ class Problem(Plan):
         R = x.shape[0]
         if x.dtype != torch.float32 or not x.is_contiguous() or tuple(x.shape) != (R, self.n) or x.device != self.device:
             raise PclsError(PCLS_E_INVALID, "rows must be a contiguous float32 (R, n) tensor on the problem's device")
-        x = x.resolve_neg()  # the kernel reads memory, which a view with a pending sign does not hold
+        if x.is_neg():  # the kernel reads memory, which holds the opposite sign
+            x = x.resolve_neg()
         X = torch.empty((self.n, round_up64(R)), dtype=torch.float32, device=self.device)
         outside = torch.empty(1, dtype=torch.int32, device=self.device)
         check(load_library().pcls_state_from_rows(self.handle, R, _tptr(x), _tptr(X), _tptr(outside), _stream()))
